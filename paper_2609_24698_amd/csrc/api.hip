@@ -142,7 +142,7 @@ WsLayout ws_layout(const tv_dims &d) {
   w.surv_key = off;
   off = align256(off + sizeof(uint32_t) * surv);
   w.surv_cnt = off;
-  off = align256(off + sizeof(int32_t) * (tseg > 1 ? nodes * tseg : 0));
+  off = align256(off + 2 * sizeof(int32_t) * (tseg > 1 ? nodes * tseg : 0));
   w.total = off;
   return w;
 }

@@ -23,7 +23,7 @@ constexpr int kAttnMaxChunk = 1280;
 
 // CSA top-k: committed entries one workgroup selects among (longer nodes are
 // cut into segments of this many entries and merged), and the survivors the
-// merge holds (512 threads x kTopkMergeKPT keys).
+// merge holds (512 x kTopkMergeKPT keys).
 constexpr int kTopkSeg = 512 * 33;
 constexpr int kTopkMergeKPT = 68;
 constexpr int kTopkMergeCap = 512 * kTopkMergeKPT;
@@ -51,7 +51,7 @@ struct WsLayout {
   size_t nkeys_rank;  // int32 [B rank][D]: the same counts by rank (0 for a skipped row)
   size_t surv_idx;    // int32 [B*D][topk segments][topk]: survivors of each top-k segment (segmented nodes only)
   size_t surv_key;    // uint32, same shape: their score keys
-  size_t surv_cnt;    // int32 [B*D][topk segments]
+  size_t surv_cnt;    // int32 [B*D][topk segments][2]: survivors, and a score key none of them exceeds
   size_t total;
   int32_t score_stride;
   SplitPlan plan;
