@@ -10,8 +10,9 @@
 //
 // General path: a persistent grid strides over the (row, 128-entry chunk)
 // list of all valid rows, so ragged lengths cost no idle workgroups.  Fast
-// path (H_idx = 8, D <= 8): one 4-wavefront workgroup per (row, 256-entry
-// chunk), the chunk body shared with the compression-and-scoring kernel.
+// path (H_idx = 8): one 4-wavefront workgroup per (row, 256-entry chunk), the
+// chunk body shared with the mask-and-scoring kernel; a tree of more than
+// eight nodes is scored in groups of eight (score_kernel_h8_groups).
 #include <algorithm>
 
 #include "score_h8.h"
@@ -165,6 +166,31 @@ __global__ void __launch_bounds__(256) score_kernel_h8(tv_dims d, CacheView c, c
                                blockIdx.x - b * chunks_per_row, sm);
 }
 
+// Trees of more than eight nodes, H_idx = 8: the fast path's chunk for each
+// group of eight nodes.  What bounds it: with few chunks the chain of one
+// (two round trips, a tile's products), so every (chunk, group) is then a
+// workgroup of its own and the keys are read again per group; with
+// kGroupGrid chunks or more the chip is full without that, and one workgroup
+// takes all groups of its chunk from keys held in registers.  The general path
+// spends its time instead in a head reduction through LDS, a barrier pair per
+// group and queries read per lane from memory.
+constexpr int kGroupGrid = 1024;
+template <bool FP8>
+__global__ void __launch_bounds__(256) score_kernel_h8_groups(tv_dims d, CacheView c,
+                                                              const uint16_t *__restrict__ q_idx,
+                                                              const uint16_t *__restrict__ w_idx,
+                                                              const int32_t *__restrict__ row_status,
+                                                              float *__restrict__ scores, int score_stride,
+                                                              int chunks_per_row, int groups, int groups_per_wg) {
+  __shared__ ScoreH8Smem<4> sm;
+  const int parts = (groups + groups_per_wg - 1) / groups_per_wg;
+  const int k = blockIdx.x / parts;
+  const int g0 = (blockIdx.x - k * parts) * groups_per_wg;
+  const int b = k / chunks_per_row;
+  score_h8_chunk<FP8, 4, true, true>(d, c, q_idx, w_idx, row_status, scores, score_stride, b, k - b * chunks_per_row,
+                                     sm, g0, std::min(groups, g0 + groups_per_wg));
+}
+
 bool score_fast_path(const tv_dims &d) { return d.H_idx == 8 && d.D <= 8; }
 
 hipError_t launch_score(const tv_dims &d, const CacheView &c, const uint16_t *q_idx, const uint16_t *w_idx,
@@ -177,6 +203,20 @@ hipError_t launch_score(const tv_dims &d, const CacheView &c, const uint16_t *q_
       score_kernel_h8<true><<<(unsigned)grid, 256, 0, s>>>(d, c, q_idx, w_idx, row_status, scores, score_stride, chunks);
     else
       score_kernel_h8<false><<<(unsigned)grid, 256, 0, s>>>(d, c, q_idx, w_idx, row_status, scores, score_stride, chunks);
+    return hipGetLastError();
+  }
+  if (d.H_idx == 8) {
+    const int chunks = std::max(1, (d.max_len / d.ratio_csa + 255) / 256);
+    const int groups = (d.D + 7) / 8;
+    const int per_wg = (int64_t)d.B * chunks >= kGroupGrid ? groups : 1;
+    const int64_t grid = (int64_t)d.B * chunks * (groups / per_wg);
+    if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
+    if (d.idx_fmt == TV_IDX_E4M3)
+      score_kernel_h8_groups<true><<<(unsigned)grid, 256, 0, s>>>(d, c, q_idx, w_idx, row_status, scores, score_stride,
+                                                                 chunks, groups, per_wg);
+    else
+      score_kernel_h8_groups<false><<<(unsigned)grid, 256, 0, s>>>(d, c, q_idx, w_idx, row_status, scores, score_stride,
+                                                                  chunks, groups, per_wg);
     return hipGetLastError();
   }
   const int64_t upper = (int64_t)d.B * ((d.max_len / d.ratio_csa + kScoreChunk - 1) / kScoreChunk);

@@ -1,6 +1,7 @@
 // CSA indexer scoring, shared pieces: key loads and the fast-path chunk body
-// (H_idx = 8, D <= 8), used by the scoring kernel and by the kernel that runs
-// the scoring beside the verify preprocess.
+// (H_idx = 8, groups of eight nodes), used by the scoring kernel and, for a
+// tree of one group, by the kernel that runs the scoring beside the verify
+// preprocess.
 //
 // score[b][i][s] = sum_h w[b][i][h] * relu(q_idx[b][i][h] . k_s) over the
 // committed entries s < len/ratio_csa, on MFMA (v_mfma_f32_32x32x16_bf16,
@@ -41,23 +42,27 @@ struct ScoreH8Smem {
   uint4 ktile[NW][32 * 8];
 };
 
-// Fast path for H_idx = 8 and D <= 8: the (node, head) rows of one tree form
-// exactly two 32-row MFMA tiles (row 8 node + head), so in the 32x32 output
-// layout a lane holds, for entry column l32, heads 4 hi + 0..3 of nodes
-// 4 tile + 0..3.  The weighted ReLU sum over a node's 8 heads is four
+// Fast path for H_idx = 8: the (node, head) rows of a group of eight nodes
+// (group g: nodes 8g .. 8g+7) form exactly two 32-row MFMA tiles (row 8 node +
+// head), so in the 32x32 output layout a lane holds, for entry column l32,
+// heads 4 hi + 0..3 of nodes 8g + 4 tile + 0..3.  The weighted ReLU sum over a node's 8 heads is four
 // in-lane terms plus the other half-wave's four (one shuffle), in fixed order.
-// The workgroup scores chunk ch of row b: NW wavefronts x 64 entries.  The
+// The workgroup scores chunk ch of row b (NW wavefronts x 64 entries) for the
+// node groups g0 .. g1 - 1, the keys held in registers and each next group's
+// queries loaded under the products of the one before; without kMulti the tree
+// is one group (D <= 8).  The
 // loads a chunk needs (row status, length, pool base, indexer weights, then
 // queries and keys) are issued as early as their addresses are known, so a
 // chunk costs two memory round trips.  kStatus: a row whose status is not
 // TV_ROW_OK is skipped (only where nothing writes the status meanwhile, so the
 // exit is workgroup-uniform; the length exits always are).
-template <bool FP8, int NW, bool kStatus>
+template <bool FP8, int NW, bool kStatus, bool kMulti = false>
 __device__ __forceinline__ void score_h8_chunk(const tv_dims &d, const CacheView &c,
                                                const uint16_t *__restrict__ q_idx,
                                                const uint16_t *__restrict__ w_idx,
                                                const int32_t *__restrict__ row_status, float *__restrict__ scores,
-                                               int score_stride, int b, int ch, ScoreH8Smem<NW> &sm) {
+                                               int score_stride, int b, int ch, ScoreH8Smem<NW> &sm, int g0 = 0,
+                                               int g1 = 1) {
   constexpr int kChunk = NW * 64;
   constexpr int kQU = (512 + 64 * NW - 1) / (64 * NW);  // 16-byte query pieces per thread (64 rows x 8)
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -67,7 +72,12 @@ __device__ __forceinline__ void score_h8_chunk(const tv_dims &d, const CacheView
   const int32_t L = c.len[b];
   const bool flat = d.page_size == 0;
   const int64_t c4b = flat ? c.c4_base[b] : 0;
-  const float wv_ = tid < M ? bf2f(w_idx[(int64_t)b * M + tid]) : 0.f;
+  // Row r of group g is query row 64 g + r of the tree; rows past M are zero.
+  auto weight = [&](int g) {
+    const int r = 64 * g + tid;
+    return tid < 64 && r < M ? bf2f(w_idx[(int64_t)b * M + r]) : 0.f;
+  };
+  float wv_ = weight(kMulti ? g0 : 0);
   if (status != TV_ROW_OK || !len_ok(L, d.max_len)) return;
   const int n4 = L / d.ratio_csa;
   const int e0 = ch * kChunk + wv * 64;
@@ -77,15 +87,25 @@ __device__ __forceinline__ void score_h8_chunk(const tv_dims &d, const CacheView
   // channels 16 ks + 8 hi of its row.  In a tile, 16-byte slot c of row r sits
   // at slot c ^ (r & 7), so the row writes and the column reads are free of
   // bank conflicts.
-  // A: the tree's 64 (node, head) query rows, loaded once for the workgroup
+  // A: a group's 64 (node, head) query rows, loaded once for the workgroup
   // (piece t: row t / 8, slot t % 8) into a shared tile.
   uint4 qr[kQU];
+  auto load_queries = [&](int g) {
 #pragma unroll
-  for (int u = 0; u < kQU; ++u) {
-    const int t = tid + u * 64 * NW, r = t >> 3;
-    qr[u] = (t < 512 && r < M) ? reinterpret_cast<const uint4 *>(q_idx + ((int64_t)b * M + r) * 64)[t & 7]
-                               : make_uint4(0, 0, 0, 0);
-  }
+    for (int u = 0; u < kQU; ++u) {
+      const int t = tid + u * 64 * NW, r = 64 * g + (t >> 3);
+      qr[u] = (t < 512 && r < M) ? reinterpret_cast<const uint4 *>(q_idx + ((int64_t)b * M + r) * 64)[t & 7]
+                                 : make_uint4(0, 0, 0, 0);
+    }
+  };
+  auto stage_queries = [&]() {
+#pragma unroll
+    for (int u = 0; u < kQU; ++u) {
+      const int t = tid + u * 64 * NW, r = t >> 3;
+      if (t < 512) sm.qtile[r * 8 + ((t & 7) ^ (r & 7))] = qr[u];
+    }
+  };
+  load_queries(kMulti ? g0 : 0);
   // B: the wavefront's 64 keys, through its own 32-row tile in two halves.
   // Every load is issued (entries past the row re-read its last one, which
   // exists: n4 > 0 here) and dead lanes are zeroed afterwards, so no branch
@@ -104,11 +124,7 @@ __device__ __forceinline__ void score_h8_chunk(const tv_dims &d, const CacheView
 #pragma unroll
   for (int u = 0; u < 8; ++u)
     if (e0 + 8 * u + (lane >> 3) >= n4) kr[u] = make_uint4(0, 0, 0, 0);
-#pragma unroll
-  for (int u = 0; u < kQU; ++u) {
-    const int t = tid + u * 64 * NW, r = t >> 3;
-    if (t < 512) sm.qtile[r * 8 + ((t & 7) ^ (r & 7))] = qr[u];
-  }
+  stage_queries();
   bf16x8 kb[2][4];
 #pragma unroll
   for (int cc = 0; cc < 2; ++cc) {
@@ -122,38 +138,47 @@ __device__ __forceinline__ void score_h8_chunk(const tv_dims &d, const CacheView
     for (int ks = 0; ks < 4; ++ks)
       kb[cc][ks] = __builtin_bit_cast(bf16x8, sm.ktile[wv][l32 * 8 + ((2 * ks + hi) ^ (l32 & 7))]);
   }
-  if (tid < 64) sm.wsh[tid] = wv_;
-  __syncthreads();
-  bf16x8 qa[2][4];
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int r = t * 32 + l32;
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-      qa[t][ks] = __builtin_bit_cast(bf16x8, sm.qtile[r * 8 + ((2 * ks + hi) ^ (r & 7))]);
-  }
-#pragma unroll
-  for (int cc = 0; cc < 2; ++cc) {
-    const int e = e0 + cc * 32 + l32;
-    const bool live = e < n4;
+  for (int g = g0;;) {
+    if (tid < 64) sm.wsh[tid] = wv_;
+    __syncthreads();
+    if (kMulti && g + 1 < g1) {  // in flight under this group's products
+      load_queries(g + 1);
+      wv_ = weight(g + 1);
+    }
+    bf16x8 qa[2][4];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      f32x16 acc = f32x16{};
+      const int r = t * 32 + l32;
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[t][ks], kb[cc][ks], acc, 0, 0, 0);
-      // head reduction of node 4t + J: rows 8J + 4hi + r of the tile, the
-      // two halves combined in a fixed order
+      for (int ks = 0; ks < 4; ++ks)
+        qa[t][ks] = __builtin_bit_cast(bf16x8, sm.qtile[r * 8 + ((2 * ks + hi) ^ (r & 7))]);
+    }
 #pragma unroll
-      for (int J = 0; J < 4; ++J) {
-        const int nd = 4 * t + J;
-        float sp = 0.f;
+    for (int cc = 0; cc < 2; ++cc) {
+      const int e = e0 + cc * 32 + l32;
+      const bool live = e < n4;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sp += sm.wsh[8 * nd + 4 * hi + r] * fmaxf(acc[4 * J + r], 0.f);
-        const float other = __shfl_xor(sp, 32, 64);
-        const float sfull = hi == 0 ? sp + other : other + sp;
-        if (hi == (J & 1) && nd < d.D && live) scores[((int64_t)b * d.D + nd) * score_stride + e] = sfull;
+      for (int t = 0; t < 2; ++t) {
+        f32x16 acc = f32x16{};
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[t][ks], kb[cc][ks], acc, 0, 0, 0);
+        // head reduction of the group's node 4t + J: rows 8J + 4hi + r of the tile, the
+        // two halves combined in a fixed order
+#pragma unroll
+        for (int J = 0; J < 4; ++J) {
+          const int nl = 4 * t + J, nd = nl + (kMulti ? 8 * g : 0);
+          float sp = 0.f;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) sp += sm.wsh[8 * nl + 4 * hi + r] * fmaxf(acc[4 * J + r], 0.f);
+          const float other = __shfl_xor(sp, 32, 64);
+          const float sfull = hi == 0 ? sp + other : other + sp;
+          if (hi == (J & 1) && nd < d.D && live) scores[((int64_t)b * d.D + nd) * score_stride + e] = sfull;
+        }
       }
     }
+    if (!kMulti || ++g >= g1) break;
+    __syncthreads();  // the group's queries and weights are read out
+    stage_queries();
   }
 }
 
