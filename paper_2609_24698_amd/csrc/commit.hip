@@ -217,67 +217,194 @@ __global__ void __launch_bounds__(256) commit_kernel(tv_dims d, tv_cache c, cons
                    primary_last, b, status, sm);
 }
 
-// The commits of several layers that share a tree, one workgroup per row
-// walking the layers in order: a row that fails in one layer is skipped by
-// every later one, as with one call per layer, and one launch replaces a
-// launch per layer (the graph round's commits).  The accepted path is the
-// row's and is resolved once; each layer's length, capacities and pool bases
-// are loaded while the layer before it copies.
-__global__ void __launch_bounds__(256) commit_layers_kernel(tv_dims d, CommitLayers ls, const uint64_t *__restrict__ anc,
-                                                            const int32_t *__restrict__ depth,
-                                                            const int32_t *__restrict__ accepted_last,
-                                                            int32_t *__restrict__ accept_nodes,
-                                                            int32_t *__restrict__ accept_len,
-                                                            int32_t *__restrict__ row_status,
-                                                            const int32_t *__restrict__ primary_last) {
-  __shared__ CommitSmem sm;
-  const int b = blockIdx.x, tid = threadIdx.x;
+// The commits of several layers that share a tree, one workgroup per row: one
+// launch replaces a launch per layer (the graph round's commits).  The
+// accepted path is the row's and is resolved once.  As with one call per layer
+// in order, a row stops at the first layer that fails it: the layers before it
+// are committed, it and the later ones are left as they were.
+//
+// What bounds it: dependent round trips and barriers (a row's copies are tens
+// of kilobytes a layer).  The layers therefore share out the workgroup's
+// sixteen wavefronts instead of following each other: every team of
+// wavefronts checks and resolves its own layers, one barrier publishes the
+// verdicts, and each team copies its layers with no further barrier.  Sixteen
+// rows of six layers took 25.7 us layer after layer and take 8.9.
+constexpr int kCommitNW = 16;
+
+struct CommitLayersSmem {
+  int32_t verdict[kCommitMaxLayers];
+  int32_t path[64];
+  // per wavefront, the tables of the layer it copies: by path depth (raw-row
+  // index), and by entry (pool slot and path node of CSA, HCA entries)
+  int64_t raw_at[kCommitNW][64], slot_at[2][kCommitNW][64];
+  int32_t ent[2][kCommitNW][64];
+};
+static_assert(kCommitMaxLayers <= 2 * kCommitNW, "a team takes at most two layers");
+
+__global__ void __launch_bounds__(kCommitNW * 64) commit_layers_kernel(
+    tv_dims d, CommitLayers ls, const uint64_t *__restrict__ anc, const int32_t *__restrict__ depth,
+    const int32_t *__restrict__ accepted_last, int32_t *__restrict__ accept_nodes, int32_t *__restrict__ accept_len,
+    int32_t *__restrict__ row_status, const int32_t *__restrict__ primary_last) {
+  __shared__ CommitLayersSmem sm;
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t rb = (int64_t)b * d.D;
   const bool flat = d.page_size == 0;
-  int32_t status = row_status[b];
+  // Teams of `waves` wavefronts, a layer each while there are enough; team t
+  // takes layers t and t + teams.
+  const int waves = std::max(1, kCommitNW / ls.n);
+  const int teams = std::min(ls.n, kCommitNW);
+  const int team = wv / waves;
+  const bool active = team < teams;
+  const int32_t status = row_status[b];
   const int32_t last = accepted_last[b];
   const int32_t P = primary_last ? primary_last[b] : -1;
-  const int32_t dt = tid < d.D ? depth[rb + tid] : 0;
-  auto layer_state = [&](int l, int32_t &L, int32_t &cap4, int32_t &cap128, int64_t &base4, int64_t &base128) {
-    const tv_cache &c = ls.l[l].cache;
-    L = c.len[b];
-    cap4 = flat ? c.c4_cap[b] : 0;
-    cap128 = flat ? c.c128_cap[b] : 0;
-    base4 = flat ? c.c4_base[b] : 0;
-    base128 = flat ? c.c128_base[b] : 0;
-  };
-  int32_t L, cap4, cap128;
-  int64_t base4, base128;
-  layer_state(0, L, cap4, cap128, base4, base128);
+  const int32_t dl = lane < d.D ? depth[rb + lane] : 0;
+  struct Layer {  // lane t: the destinations of the path node at depth t
+    int32_t L;
+    int32_t cap4, cap128;
+    int64_t base4, base128;
+    int64_t raw, s4, s128;
+  } st[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int l = team + u * teams;
+    if (active && l < ls.n) {
+      const tv_cache &c = ls.l[l].cache;
+      st[u].L = c.len[b];
+      st[u].cap4 = flat ? c.c4_cap[b] : 0;
+      st[u].cap128 = flat ? c.c128_cap[b] : 0;
+      st[u].base4 = flat ? c.c4_base[b] : 0;
+      st[u].base128 = flat ? c.c128_base[b] : 0;
+    }
+  }
   if (status != TV_ROW_OK) return;
   const bool last_ok = last >= 0 && last < d.D;
   const uint64_t m = last_ok ? anc[rb + last] : 0ull;
   const uint64_t chain = (P >= 0 && P < d.D) ? anc[rb + P] : 0ull;
   const int a = last_ok ? depth[rb + last] + 1 : 0;
-  if (tid < d.D && ((m >> tid) & 1ull)) sm.path[dt] = tid;
-  bool committed = false;
-  for (int l = 0; l < ls.n; ++l) {
-    if (!len_ok(L, d.max_len)) {
-      if (tid == 0) row_status[b] = TV_ROW_BAD_LEN;
-      return;
+  if (wv == 0 && lane < d.D && ((m >> lane) & 1ull)) sm.path[dl] = lane;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int l = team + u * teams;
+    if (!active || l >= ls.n) continue;
+    const tv_cache &c = ls.l[l].cache;
+    Layer &x = st[u];
+    x.raw = x.s4 = x.s128 = -1;
+    int32_t v = !len_ok(x.L, d.max_len) ? TV_ROW_BAD_LEN : !last_ok ? TV_ROW_BAD_ACCEPT : TV_ROW_OK;
+    if (v == TV_ROW_OK) {
+      bool bad = false;
+      if (lane < a) {
+        const int64_t p = (int64_t)x.L + lane;  // path node at depth `lane` stands at L + lane
+        x.raw = raw_index(d, c.page_table, b, p);
+        bad |= x.raw < 0;
+        if ((p + 1) % d.ratio_csa == 0) {
+          const int64_t e = (p + 1) / d.ratio_csa - 1;
+          x.s4 = flat ? (e < x.cap4 ? x.base4 + e : -1)
+                      : pool_slot(d, c.page_table, nullptr, nullptr, b, e, d.ratio_csa);
+          bad |= x.s4 < 0;
+        }
+        if ((p + 1) % d.ratio_hca == 0) {
+          const int64_t e = (p + 1) / d.ratio_hca - 1;
+          x.s128 = flat ? (e < x.cap128 ? x.base128 + e : -1)
+                        : pool_slot(d, c.page_table, nullptr, nullptr, b, e, d.ratio_hca);
+          bad |= x.s128 < 0;
+        }
+      }
+      if (__any(bad)) v = TV_ROW_CAPACITY;
     }
-    if (!last_ok) {
-      if (tid == 0) row_status[b] = TV_ROW_BAD_ACCEPT;
-      return;
-    }
+    if (lane == 0 && wv == team * waves) sm.verdict[l] = v;
+  }
+  __syncthreads();  // verdicts and path are visible, and every layer's length is read
+  const int32_t vl = lane < ls.n ? sm.verdict[lane] : TV_ROW_OK;
+  const uint64_t failed = __ballot(vl != TV_ROW_OK);
+  const int n_ok = failed ? __ffsll((unsigned long long)failed) - 1 : ls.n;
+  if (failed && tid == 0) row_status[b] = sm.verdict[n_ok];
+  if (n_ok > 0 && wv == 0) {  // every layer's commit writes the same path
+    if (lane < d.D) accept_nodes[rb + lane] = lane < a ? sm.path[lane] : -1;
+    if (lane == 0) accept_len[b] = a;
+  }
+  // Copies of a layer as one list of 16-byte chunks: raw rows of the path into
+  // the ring, CSA entries (latent row, then indexer key) and HCA entries into
+  // their pool slots.  A lane's loads all go out before its stores.
+  const int d_u = d.d_row + d.d_idx;
+  const int cpr = d_u / 8, c128c = d.d_row / 8;
+  int64_t *raw_at = sm.raw_at[wv];
+  int64_t *slot4 = sm.slot_at[0][wv], *slot128 = sm.slot_at[1][wv];
+  int32_t *node4 = sm.ent[0][wv], *node128 = sm.ent[1][wv];
+  const int my_node = lane < a ? sm.path[lane] : 0;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int l = team + u * teams;
+    if (!active || l >= n_ok) continue;
     const CommitLayer &cl = ls.l[l];
-    const int32_t Lc = L;
-    const int32_t c4c = cap4, c128c = cap128;
-    const int64_t b4c = base4, b128c = base128;
-    if (l + 1 < ls.n) layer_state(l + 1, L, cap4, cap128, base4, base128);  // in flight during this layer's copies
-    if (commit_layer(d, cl.cache, cl.tree_u, cl.scr_c4, cl.scr_c128, row_status, b, Lc, a, chain, c4c, c128c, b4c,
-                     b128c, sm) != TV_ROW_OK)
-      return;
-    if (!committed) {  // every layer's commit writes the same path
-      committed = true;
-      if (tid < d.D) accept_nodes[rb + tid] = tid < a ? sm.path[tid] : -1;
-      if (tid == 0) accept_len[b] = a;
+    const tv_cache &c = cl.cache;
+    const Layer &x = st[u];
+    const bool e4 = x.s4 >= 0 && !((chain >> my_node) & 1ull), e128 = x.s128 >= 0;
+    const uint64_t b4 = __ballot(e4), b128 = __ballot(e128);
+    const uint64_t below = (1ull << lane) - 1ull;
+    // this wavefront's own tables: its LDS operations stay in order
+    raw_at[lane] = x.raw;
+    if (e4) {
+      slot4[__popcll(b4 & below)] = x.s4;
+      node4[__popcll(b4 & below)] = my_node;
     }
+    if (e128) {
+      slot128[__popcll(b128 & below)] = x.s128;
+      node128[__popcll(b128 & below)] = my_node;
+    }
+    __builtin_amdgcn_wave_barrier();
+    const int n_ring = a * cpr, n4 = __popcll(b4) * cpr, total = n_ring + n4 + __popcll(b128) * c128c;
+    constexpr int kBatch = 8;
+    for (int e0 = (wv - team * waves) * 64; e0 < total; e0 += kBatch * 64 * waves) {
+      uint4 v[kBatch];
+      uint16_t *dst[kBatch];
+      uint32_t narrow = 0u;  // chunks stored as E4M3 codes: 8 bytes
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) {
+        const int e = e0 + k * 64 * waves + lane;
+        dst[k] = nullptr;
+        v[k] = make_uint4(0, 0, 0, 0);
+        if (e < n_ring) {
+          const int t = e / cpr, ch = (e - t * cpr) * 8;
+          v[k] = *reinterpret_cast<const uint4 *>(cl.tree_u + (rb + sm.path[t]) * d_u + ch);
+          dst[k] = c.ring + raw_at[t] * d_u + ch;
+        } else if (e < n_ring + n4) {
+          const int y = e - n_ring, t = y / cpr, ch = (y - t * cpr) * 8;
+          const int64_t slot = slot4[t];
+          v[k] = *reinterpret_cast<const uint4 *>(cl.scr_c4 + (rb + node4[t]) * d_u + ch);
+          if (ch < d.d_row) {
+            dst[k] = c.c4 + slot * d.d_row + ch;
+          } else if (d.idx_fmt == TV_IDX_E4M3) {
+            dst[k] = reinterpret_cast<uint16_t *>(reinterpret_cast<uint8_t *>(c.c4_idx) + slot * d.d_idx +
+                                                  (ch - d.d_row));
+            narrow |= 1u << k;
+          } else {
+            dst[k] = c.c4_idx + slot * d.d_idx + (ch - d.d_row);
+          }
+        } else if (e < total) {
+          const int y = e - n_ring - n4, t = y / c128c, ch = (y - t * c128c) * 8;
+          v[k] = *reinterpret_cast<const uint4 *>(cl.scr_c128 + (rb + node128[t]) * d.d_row + ch);
+          dst[k] = c.c128 + slot128[t] * d.d_row + ch;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) {
+        if (!dst[k]) continue;
+        if ((narrow >> k) & 1u) {  // the scratch holds E4M3 values in bfloat16: narrow them exactly
+          uint2 w;
+          w.x = bf16_to_e4m3(v[k].x & 0xFFFF) | (bf16_to_e4m3(v[k].x >> 16) << 8) |
+                (bf16_to_e4m3(v[k].y & 0xFFFF) << 16) | (bf16_to_e4m3(v[k].y >> 16) << 24);
+          w.y = bf16_to_e4m3(v[k].z & 0xFFFF) | (bf16_to_e4m3(v[k].z >> 16) << 8) |
+                (bf16_to_e4m3(v[k].w & 0xFFFF) << 16) | (bf16_to_e4m3(v[k].w >> 16) << 24);
+          *reinterpret_cast<uint2 *>(dst[k]) = w;
+        } else {
+          *reinterpret_cast<uint4 *>(dst[k]) = v[k];
+        }
+      }
+    }
+    if (lane == 0 && wv == team * waves) c.len[b] = x.L + a;
+    __builtin_amdgcn_wave_barrier();  // the tables are read out
   }
 }
 
@@ -285,7 +412,7 @@ hipError_t launch_commit_layers(const tv_dims &d, const CommitLayers &ls, const 
                                 const int32_t *accepted_last, int32_t *accept_nodes, int32_t *accept_len,
                                 int32_t *row_status, const int32_t *primary_last, hipStream_t s) {
   if (ls.n < 1 || ls.n > kCommitMaxLayers) return hipErrorInvalidValue;
-  commit_layers_kernel<<<d.B, 256, 0, s>>>(d, ls, anc, depth, accepted_last, accept_nodes, accept_len, row_status,
+  commit_layers_kernel<<<d.B, kCommitNW * 64, 0, s>>>(d, ls, anc, depth, accepted_last, accept_nodes, accept_len, row_status,
                                            primary_last);
   return hipGetLastError();
 }
