@@ -83,37 +83,71 @@ static tv_status check_device() {
   return verdict[dev] == 1 ? TV_OK : TV_ERR_DEVICE;
 }
 
-// Attention workgroups the split plan aims for, and the fewest keys a split
-// takes when splitting is optional.  Every split pays a prologue (key table,
-// first tiles, queries), an epilogue and a partial-output round trip through
-// memory, so nodes are split only while there are fewer workgroups than
-// compute units to fill.
-#ifndef TV_ATTN_TARGET_WG
-#define TV_ATTN_TARGET_WG 256
-#endif
-#ifndef TV_ATTN_MIN_CHUNK
-#define TV_ATTN_MIN_CHUNK 256
-#endif
+// How the attention's time depends on the split, per head shape (microseconds
+// at the warm clock, fitted to steps with forced split counts): a workgroup's
+// prologue and epilogue, one 32-key tile, the combine launch with the float32
+// epilogue it needs, one partial written and merged; and the workgroups an XCD
+// holds at once (32 compute units; the LDS leaves the 64-head kernel one each).
+struct SplitCost {
+  float fixed, tile, combine, partial;
+  int slots;
+};
+static SplitCost split_cost(const tv_dims &d) {
+  return d.H == 64 ? SplitCost{8.0f, 0.8f, 5.0f, 0.03f, 32} : SplitCost{6.0f, 0.65f, 4.0f, 0.002f, 64};
+}
 
-SplitPlan split_plan(const tv_dims &d) {
+static SplitPlan plan_of(int64_t mk, int64_t splits) {
   SplitPlan p;
-  const int64_t mk = (int64_t)d.topk + d.max_len / d.ratio_hca + d.D + d.window;
-  p.max_keys = (int32_t)mk;
-  const int64_t nodes = (int64_t)d.B * d.D;
-  int64_t splits = std::max<int64_t>(1, (TV_ATTN_TARGET_WG + nodes - 1) / nodes);
-  splits = std::min<int64_t>(splits, std::max<int64_t>(1, mk / TV_ATTN_MIN_CHUNK));
-  splits = std::max<int64_t>(splits, (mk + kAttnMaxChunk - 1) / kAttnMaxChunk);  // pointer table bound
   const int64_t chunk = ((mk + splits - 1) / splits + 31) / 32 * 32;
+  p.max_keys = (int32_t)mk;
   p.chunk = (int32_t)chunk;
   p.splits = (int32_t)((mk + chunk - 1) / chunk);
   return p;
 }
 
+// The cheapest split count by the cost above: the fewest the pointer table
+// allows, or one of those with which all workgroups still run at once (one
+// more round of workgroups costs more than any split saves).  An XCD gets whole
+// rows when there are 8 or more (unit_of), so the fullest XCD decides: 12 rows
+// of 7 nodes fill 14 of its 32 compute units unsplit and need two rounds in
+// three splits (step 55.5 us unsplit, 58.0 in two, 68.1 in three).  Measured
+// otherwise, 64 heads, splits: step in us (712 keys): 8 nodes 1: 42.2, 2: 37.9,
+// 4: 33.8, 8: 33.0, 12: 34.6; 128 nodes 1: 49.7, 2: 54.1; 160 nodes 1: 51.7,
+// 2: 74.3 (two rounds); 192 nodes of 32 a row 1: 89.1, 2: 115.3.  8 heads: 8
+// nodes of 776 keys 1: 38.1, 3: 30.2, 8: 26.7; 222 nodes of 404 keys 1: 39.4,
+// 2: 40.9.
+SplitPlan split_plan(const tv_dims &d) {
+  const SplitCost k = split_cost(d);
+  const int64_t mk = (int64_t)d.topk + d.max_len / d.ratio_hca + d.D + d.window;
+  const int64_t nodes = (int64_t)d.B * d.D;
+  auto per_xcd = [&](int64_t splits) {
+    if (d.B >= 8) return (int64_t)((d.B + 7) / 8) * d.D * splits;
+    return (nodes * attn_padded_splits(d.B, (int)splits) + 7) / 8;
+  };
+  auto cost = [&](const SplitPlan &p) {
+    const int64_t rounds = (per_xcd(p.splits) + k.slots - 1) / k.slots;
+    return (float)rounds * (k.fixed + k.tile * (float)(p.chunk / 32)) +
+           (p.splits > 1 ? k.combine + k.partial * (float)(nodes * p.splits) : 0.0f);
+  };
+  const int64_t least = (mk + kAttnMaxChunk - 1) / kAttnMaxChunk;  // pointer table bound
+  SplitPlan best = plan_of(mk, least);
+  float best_cost = cost(best);
+  for (int64_t s = least + 1; s <= (mk + 31) / 32 && per_xcd(s) <= k.slots; ++s) {
+    const SplitPlan p = plan_of(mk, s);
+    const float c = cost(p);
+    if (c < best_cost) {
+      best = p;
+      best_cost = c;
+    }
+  }
+  return best;
+}
+
 static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-WsLayout ws_layout(const tv_dims &d) {
+static WsLayout ws_layout_of(const tv_dims &d, const SplitPlan &plan) {
   WsLayout w;
-  w.plan = split_plan(d);
+  w.plan = plan;
   const int64_t nodes = (int64_t)d.B * d.D;
   w.score_stride = (int32_t)((d.max_len / d.ratio_csa + 63) / 64 * 64);
   size_t off = 0;
@@ -145,6 +179,17 @@ WsLayout ws_layout(const tv_dims &d) {
   off = align256(off + 2 * sizeof(int32_t) * (tseg > 1 ? nodes * tseg : 0));
   w.total = off;
   return w;
+}
+
+// A split that would take the workspace past the no-alloc entry's array, where
+// the fewest splits fit it, is not worth that entry's refusal.
+WsLayout ws_layout(const tv_dims &d) {
+  const WsLayout w = ws_layout_of(d, split_plan(d));
+  const int64_t mk = w.plan.max_keys;
+  const int64_t least = (mk + kAttnMaxChunk - 1) / kAttnMaxChunk;
+  if (w.total <= TV_NOALLOC_SCRATCH_BYTES || w.plan.splits <= least) return w;
+  const WsLayout fewest = ws_layout_of(d, plan_of(mk, least));
+  return fewest.total <= TV_NOALLOC_SCRATCH_BYTES ? fewest : w;
 }
 
 // ---- kernel timing -------------------------------------------------------
