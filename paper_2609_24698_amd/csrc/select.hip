@@ -49,11 +49,20 @@ __device__ __forceinline__ uint64_t umax64(uint64_t a, uint64_t b) { return a > 
 // workgroup maximum then look for its first index, so the search costs one
 // wavefront.
 // kVec: vocab % 8 == 0, so every node's logits start on a 16-byte boundary.
+// Otherwise a node's logits start `off` logits past one (the buffer itself is
+// aligned), and its chunks are cut on the boundaries before: chunk ch holds
+// logits 8192 ch - off and on, in the same whole 16-byte pieces, with the
+// neighbours' logits in a node's first and last piece masked; a node's last
+// chunk takes one piece more where the shift pushes the end past it, and a
+// piece that would cross the end of the buffer is read logit by logit.  (512
+// nodes of 129,281 logits took 72 us with a 2-byte load a logit and take 28; of
+// 129,280, 25.)
 template <bool kVec>
 __global__ void __launch_bounds__(kSelNT) argmax_kernel(const uint16_t *__restrict__ logits, int32_t vocab,
-                                                        int chunks, uint64_t *__restrict__ part) {
+                                                        int chunks, int64_t nodes, uint64_t *__restrict__ part) {
   constexpr int kWaves = kSelNT / 64;
-  constexpr int kWords = kVec ? 4 * kSelLoads : kSelChunk / kSelNT / 2;  // 32-bit words (logit pairs) per thread
+  constexpr int kPieces = kVec ? kSelLoads : kSelLoads + 1;  // per thread; the last one: thread 0 of a last chunk
+  constexpr int kWords = 4 * kPieces;                         // 32-bit words (logit pairs) per thread
   constexpr uint32_t kNegInfPair = 0xFF80FF80u;  // out-of-range logits never beat an in-range one
   __shared__ float red_max[kWaves];
   __shared__ int red_nan[kWaves];
@@ -62,32 +71,36 @@ __global__ void __launch_bounds__(kSelNT) argmax_kernel(const uint16_t *__restri
   const int ch = blockIdx.x - (int)node * chunks;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const uint16_t *row = logits + node * vocab;
-  const int c0 = ch * kSelChunk;
+  const int c0 = ch * kSelChunk - (kVec ? 0 : (int)((node * vocab) & 7));
   // index of the logit in the low half of word j of this thread
-  auto first_of = [&](int j) {
-    if constexpr (kVec)
-      return c0 + ((j >> 2) * kSelNT + tid) * 8 + 2 * (j & 3);
-    else
-      return c0 + 2 * (j * kSelNT + tid);
-  };
+  auto first_of = [&](int j) { return c0 + ((j >> 2) * kSelNT + tid) * 8 + 2 * (j & 3); };
   uint32_t w[kWords];
-  if constexpr (kVec) {
+  const int64_t left = (nodes - node) * vocab;  // logits from this node's first to the buffer's end
+  auto piece_in = [&](int u) { return first_of(4 * u) < vocab && (u < kSelLoads || (tid == 0 && ch == chunks - 1)); };
 #pragma unroll
-    for (int u = 0; u < kSelLoads; ++u) {
+  for (int u = 0; u < kPieces; ++u) {
+    const int e = first_of(4 * u);
+    const uint4 v = piece_in(u) && (kVec || (int64_t)e + 8 <= left)
+                        ? *reinterpret_cast<const uint4 *>(row + e)
+                        : make_uint4(kNegInfPair, kNegInfPair, kNegInfPair, kNegInfPair);
+    w[4 * u] = v.x;
+    w[4 * u + 1] = v.y;
+    w[4 * u + 2] = v.z;
+    w[4 * u + 3] = v.w;
+  }
+  if constexpr (!kVec) {
+#pragma unroll
+    for (int u = 0; u < kPieces; ++u) {
       const int e = first_of(4 * u);
-      const uint4 v = e < vocab ? *reinterpret_cast<const uint4 *>(row + e)
-                                : make_uint4(kNegInfPair, kNegInfPair, kNegInfPair, kNegInfPair);
-      w[4 * u] = v.x;
-      w[4 * u + 1] = v.y;
-      w[4 * u + 2] = v.z;
-      w[4 * u + 3] = v.w;
-    }
-  } else {
+      if (!piece_in(u) || (e >= 0 && e + 8 <= vocab)) continue;
 #pragma unroll
-    for (int j = 0; j < kWords; ++j) {
-      const int e = first_of(j);
-      const uint32_t lo = e < vocab ? row[e] : 0xFF80u, hi = e + 1 < vocab ? row[e + 1] : 0xFF80u;
-      w[j] = lo | (hi << 16);
+      for (int k = 0; k < 4; ++k) {
+        const int lo = e + 2 * k, hi = lo + 1;
+        if ((int64_t)e + 8 > left)  // the buffer's last piece
+          w[4 * u + k] = (lo < vocab ? row[lo] : 0xFF80u) | ((hi < vocab ? row[hi] : 0xFF80u) << 16);
+        if (lo < 0 || lo >= vocab) w[4 * u + k] = (w[4 * u + k] & 0xFFFF0000u) | 0xFF80u;
+        if (hi < 0 || hi >= vocab) w[4 * u + k] = (w[4 * u + k] & 0xFFFFu) | 0xFF800000u;
+      }
     }
   }
   float m = -INFINITY;
@@ -119,8 +132,8 @@ __global__ void __launch_bounds__(kSelNT) argmax_kernel(const uint16_t *__restri
     for (int j = kWords - 1; j >= 0; --j) {  // backwards: the last hit is the first index
       const float lo = __uint_as_float(w[j] << 16), hi = __uint_as_float(w[j] & 0xFFFF0000u);
       const int e = first_of(j);
-      if (any_nan ? (hi != hi) : (hi == M)) idx = e + 1 < vocab ? e + 1 : idx;
-      if (any_nan ? (lo != lo) : (lo == M)) idx = e < vocab ? e : idx;
+      if (any_nan ? (hi != hi) : (hi == M)) idx = (unsigned)(e + 1) < (unsigned)vocab ? e + 1 : idx;
+      if (any_nan ? (lo != lo) : (lo == M)) idx = (unsigned)e < (unsigned)vocab ? e : idx;
     }
     idx = wave_min_i32(idx);  // the wavefront's condition is uniform: every lane is here
   }
@@ -180,9 +193,9 @@ hipError_t launch_argmax(const tv_dims &d, const uint16_t *logits, int32_t vocab
   const int64_t grid = (int64_t)d.B * d.D * chunks;
   if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
   if (vocab % 8 == 0)
-    argmax_kernel<true><<<(unsigned)grid, kSelNT, 0, s>>>(logits, vocab, chunks, part);
+    argmax_kernel<true><<<(unsigned)grid, kSelNT, 0, s>>>(logits, vocab, chunks, (int64_t)d.B * d.D, part);
   else
-    argmax_kernel<false><<<(unsigned)grid, kSelNT, 0, s>>>(logits, vocab, chunks, part);
+    argmax_kernel<false><<<(unsigned)grid, kSelNT, 0, s>>>(logits, vocab, chunks, (int64_t)d.B * d.D, part);
   return hipGetLastError();
 }
 
