@@ -380,8 +380,8 @@ static tv_status verify_impl(const tv_dims *dims, const tv_cache *cache, const u
 }
 
 // One layer's verify preprocess (with_mask), compression and verification.
-// With the scoring's fast path, a flat pool and the split compression, no
-// kernel of its own is left for the compression: the first launch runs the
+// With the scoring's fast path and the split compression, no kernel of its own
+// is left for the compression (a paged step of 12 rows spent 7.7 us in it): the first launch runs the
 // mask (with_mask), the CSA entries (a wavefront per node; beside the mask
 // from the parent array) and the indexer scoring (it reads neither the masks
 // nor the scratch), and the top-k's launch also runs the HCA entries (the
@@ -392,7 +392,7 @@ static tv_status verify_impl(const tv_dims *dims, const tv_cache *cache, const u
 // checked.
 static tv_status layer_step(const tv_dims *d, const tv_round &r, const tv_layer &L, bool with_mask,
                             hipStream_t stream) {
-  const bool split = score_fast_path(*d) && d->page_size == 0 && compress_split(*d);
+  const bool split = score_fast_path(*d) && compress_split(*d);
   const bool fused = (with_mask && score_fast_path(*d)) || split;
   if (fused) {
     const WsLayout w = ws_layout(*d);

@@ -24,14 +24,23 @@ __device__ __forceinline__ float dot8(const float *g, uint4 v) {
          g[4] * bf2f_lo(v.z) + g[5] * bf2f_hi(v.z) + g[6] * bf2f_lo(v.w) + g[7] * bf2f_hi(v.w);
 }
 
+// True when the block of R tokens that a node at position p closes starts with
+// committed tokens whose page is not allocated (paged pool: a page holds whole
+// blocks, so the block's first position stands for all of them).
+__device__ __forceinline__ bool block_lost(const tv_dims &d, const int32_t *table, int b, int32_t L, int64_t p, int R) {
+  const int64_t q0 = p - R + 1;
+  return (p + 1) % R == 0 && q0 < L && page_of(d, table, b, q0 / d.page_size) < 0;
+}
+
 // The short-block path, run by one wavefront per node (see above); it uses
-// no workgroup barrier.  q0 is the block's first position, R its token count,
+// no workgroup barrier.  A committed row of no allocated page fails the row
+// (row_status not NULL) or leaves the entry out (NULL).  q0 is the block's first position, R its token count,
 // m the node's ancestor mask, dj the depth of node `lane`, path an LDS array
 // of the wavefront's own.
 __device__ void compress_short(const tv_dims &d, const CacheView &c, const uint16_t *__restrict__ tree_u,
                                const uint16_t *__restrict__ gate_w, int b, int64_t node, int32_t L, int64_t q0, int R,
                                uint64_t m, int32_t dj, int32_t *path, uint16_t *__restrict__ scr_c4,
-                               int32_t *__restrict__ row_status, int64_t pslot, uint16_t *__restrict__ pool_c4,
+                               int32_t *row_status, int64_t pslot, uint16_t *__restrict__ pool_c4,
                                uint16_t *__restrict__ pool_c4_idx) {
   const int lane = threadIdx.x & 63;
   const int d_u = d.d_row + d.d_idx, nch = d_u / 8;
@@ -49,7 +58,7 @@ __device__ void compress_short(const tv_dims &d, const CacheView &c, const uint1
     rp = tree_u + ((int64_t)b * d.D + path[qt - L]) * d_u;
   }
   if (__any(lane < R && ri < 0)) {  // a committed row whose page is not allocated
-    if (lane == 0) row_status[b] = TV_ROW_CAPACITY;
+    if (lane == 0 && row_status) row_status[b] = TV_ROW_CAPACITY;
     return;
   }
   const uintptr_t rpi = reinterpret_cast<uintptr_t>(rp);
@@ -142,9 +151,11 @@ __device__ void compress_short(const tv_dims &d, const CacheView &c, const uint1
 // wavefront can run beside the preprocess, which writes them; a row with bad
 // parents or a bad length is skipped.  Otherwise they are read from anc,
 // depth and row_status.  The wavefront writes a row status only to fail a row
-// of a paged pool (a committed row of the block in no allocated page), which
-// kSelfMask callers do not use.  `path` is the wavefront's own 64-entry LDS
-// array.
+// of a paged pool (a committed row of the block in no allocated page), and not
+// with kSelfMask, where the preprocess beside it fails such rows.  With
+// fail_hca it fails the row for the HCA block its node closes as well, for
+// callers whose HCA workgroups run beside readers of the status.  `path` is
+// the wavefront's own 64-entry LDS array.
 template <bool kSelfMask>
 __device__ __forceinline__ void csa_wave_node(const tv_dims &d, const CacheView &c, const int32_t *__restrict__ parents,
                                               const uint64_t *__restrict__ anc, const int32_t *__restrict__ depth,
@@ -152,7 +163,7 @@ __device__ __forceinline__ void csa_wave_node(const tv_dims &d, const CacheView 
                                               uint16_t *__restrict__ scr_c4, int32_t *__restrict__ row_status,
                                               const int32_t *__restrict__ primary_last,
                                               uint16_t *__restrict__ pool_c4, uint16_t *__restrict__ pool_c4_idx,
-                                              int blk, int32_t *path) {
+                                              int blk, int32_t *path, bool fail_hca = false) {
   const int b = blk / d.D;
   const int i = blk - b * d.D;
   const int lane = threadIdx.x & 63;
@@ -195,6 +206,10 @@ __device__ __forceinline__ void csa_wave_node(const tv_dims &d, const CacheView 
     if (status != TV_ROW_OK || !len_ok(L, d.max_len)) return;
   }
   const int64_t p = (int64_t)L + dep;
+  if (!kSelfMask && fail_hca && !flat && block_lost(d, c.page_table, b, L, p, d.ratio_hca)) {
+    if (lane == 0) row_status[b] = TV_ROW_CAPACITY;
+    return;
+  }
   if (((p + 1) % d.ratio_csa) != 0) return;
   const int R = d.ratio_csa;
   const int64_t slot4 = (p + 1) / d.ratio_csa - 1;
@@ -204,8 +219,8 @@ __device__ __forceinline__ void csa_wave_node(const tv_dims &d, const CacheView 
   if ((chain >> i) & 1ull)
     pslot = flat ? (slot4 < cap4 ? base4 + slot4 : -1)
                  : pool_slot(d, c.page_table, nullptr, nullptr, b, slot4, d.ratio_csa);
-  compress_short(d, c, tree_u, gate_w, b, node, L, p - R + 1, R, m, dj, path, scr_c4, row_status, pslot, pool_c4,
-                 pool_c4_idx);
+  compress_short(d, c, tree_u, gate_w, b, node, L, p - R + 1, R, m, dj, path, scr_c4,
+                 kSelfMask ? nullptr : row_status, pslot, pool_c4, pool_c4_idx);
 }
 
 // The HCA entry node `blk` closes, if it closes one, pooled by a workgroup of

@@ -12,11 +12,14 @@ namespace tv {
 // Workgroup `blk` (256 threads) takes rows 4 blk .. 4 blk + 3, one per
 // wavefront.  With `len` (and its bound max_len), a valid tree whose row
 // length is out of range gets TV_ROW_BAD_LEN, the status the compression
-// would give it next.
+// would give it next.  With `paged` (its dims, and the page table), a row that
+// closes a CSA or HCA block whose committed tokens are in no allocated page
+// gets TV_ROW_CAPACITY, likewise.
 __device__ __forceinline__ void mask_rows(int B, int D, const int32_t *__restrict__ parents,
                                           uint64_t *__restrict__ anc, int32_t *__restrict__ depth,
                                           int32_t *__restrict__ row_status, const int32_t *__restrict__ len,
-                                          int max_len, int blk, int32_t (*par)[64]) {
+                                          int max_len, int blk, int32_t (*par)[64], const tv_dims *paged = nullptr,
+                                          const int32_t *__restrict__ page_table = nullptr) {
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
   const int b = blk * 4 + w;
@@ -28,6 +31,7 @@ __device__ __forceinline__ void mask_rows(int B, int D, const int32_t *__restric
   const bool row_ok = __all(ok);
   __syncthreads();
   if (!live) return;
+  bool lost = false;
   if (i < D) {
     uint64_t m = 0;
     int32_t dep = 0;
@@ -42,9 +46,19 @@ __device__ __forceinline__ void mask_rows(int B, int D, const int32_t *__restric
     }
     anc[(int64_t)b * D + i] = m;
     depth[(int64_t)b * D + i] = dep;
+    if (paged && row_ok && len_ok(len[b], max_len)) {
+      const int32_t L = len[b];
+      const int64_t pos = (int64_t)L + dep;
+      lost = block_lost(*paged, page_table, b, L, pos, paged->ratio_csa) ||
+             block_lost(*paged, page_table, b, L, pos, paged->ratio_hca);
+    }
   }
+  const bool row_lost = __any(lost);
   if (lane == 0)
-    row_status[b] = !row_ok ? TV_ROW_BAD_PARENT : (len && !len_ok(len[b], max_len)) ? TV_ROW_BAD_LEN : TV_ROW_OK;
+    row_status[b] = !row_ok                            ? TV_ROW_BAD_PARENT
+                    : (len && !len_ok(len[b], max_len)) ? TV_ROW_BAD_LEN
+                    : row_lost                          ? TV_ROW_CAPACITY
+                                                        : TV_ROW_OK;
 }
 
 __global__ void __launch_bounds__(256) mask_kernel(int B, int D, const int32_t *__restrict__ parents,
@@ -61,7 +75,10 @@ __global__ void __launch_bounds__(256) mask_kernel(int B, int D, const int32_t *
 // meanwhile; a row the mask fails gets scores that no later step reads.
 // With the split compression's CSA entries (csa.gate_w not NULL), a
 // wavefront per node pools them between the two, deriving the node's
-// ancestors from the parent array itself (csa_wave_node<true>).  Without
+// ancestors from the parent array itself (csa_wave_node<true>); rows of a
+// paged pool that a missing page fails are failed by the mask's workgroups, or
+// without them by the CSA wavefronts, for both ratios: the HCA entries are
+// pooled beside the next launch's readers of the status.  Without
 // parents the launch has no mask workgroups: the masks and the row status
 // are already final (a later layer of the round), and the CSA wavefronts
 // read them.
@@ -88,7 +105,8 @@ __global__ void __launch_bounds__(256) mask_score_kernel(tv_dims d, const int32_
   const int nmask = parents ? (d.B + 3) / 4 : 0;
   const int blk = blockIdx.x;
   if (blk < nmask) {
-    mask_rows(d.B, d.D, parents, anc, depth, row_status, c.len, d.max_len, blk, sm.par);
+    mask_rows(d.B, d.D, parents, anc, depth, row_status, c.len, d.max_len, blk, sm.par,
+              ncsa > 0 && d.page_size > 0 ? &d : nullptr, c.page_table);
   } else if (blk < nmask + ncsa) {
     const int wv = threadIdx.x >> 6, n = (blk - nmask) * 4 + wv;
     if (n < d.B * d.D) {
@@ -97,7 +115,7 @@ __global__ void __launch_bounds__(256) mask_score_kernel(tv_dims d, const int32_
                             csa.primary_last, csa.pool_c4, csa.pool_c4_idx, n, sm.paths[wv]);
       else  // the masks and row status are final
         csa_wave_node<false>(d, c, nullptr, anc, depth, csa.tree_u, csa.gate_w, csa.scr_c4, row_status,
-                             csa.primary_last, csa.pool_c4, csa.pool_c4_idx, n, sm.paths[wv]);
+                             csa.primary_last, csa.pool_c4, csa.pool_c4_idx, n, sm.paths[wv], true);
     }
   } else {
     const int k = blk - nmask - ncsa, b = k / chunks_per_row;
@@ -113,7 +131,7 @@ hipError_t launch_mask_score(const tv_dims &d, const int32_t *parents, uint64_t 
                              uint16_t *csa_pool_c4, uint16_t *csa_pool_c4_idx, hipStream_t s) {
   if (!score_fast_path(d)) return hipErrorInvalidValue;
   const bool with_csa = csa_gate_w != nullptr;
-  if (with_csa && (!compress_split(d) || d.page_size != 0)) return hipErrorInvalidValue;
+  if (with_csa && !compress_split(d)) return hipErrorInvalidValue;
   const int chunks = std::max(1, (d.max_len / d.ratio_csa + 255) / 256);
   const int ncsa = with_csa ? (d.B * d.D + 3) / 4 : 0;
   const int64_t grid = (parents ? (int64_t)(d.B + 3) / 4 : 0) + ncsa + (int64_t)d.B * chunks;

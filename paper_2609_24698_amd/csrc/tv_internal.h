@@ -93,9 +93,10 @@ bool score_fast_path(const tv_dims &d);
 // launch_mask and launch_score (fast path) as one launch: the mask's
 // workgroups first, then the scoring chunks, which do not read the masks;
 // the mask also fails a valid tree whose length is out of range.  With
-// csa_gate_w not NULL (split compression, flat pool), the launch also pools
-// every CSA entry the tree closes into csa_scr_c4 (and the designated chain's
-// into the pool), as the compression does.  With parents NULL there is no
+// csa_gate_w not NULL (split compression), the launch also pools every CSA
+// entry the tree closes into csa_scr_c4 (and the designated chain's into the
+// pool) and fails the rows of a paged pool that lack a page of an open block,
+// as the compression does.  With parents NULL there is no
 // mask: anc, depth and row_status are inputs.
 hipError_t launch_mask_score(const tv_dims &d, const int32_t *parents, uint64_t *anc, int32_t *depth,
                              int32_t *row_status, const CacheView &c, const uint16_t *q_idx, const uint16_t *w_idx,
