@@ -84,62 +84,67 @@ static tv_status check_device() {
 }
 
 // How the attention's time depends on the split, per head shape (microseconds
-// at the warm clock, fitted to steps with forced split counts): a workgroup's
-// prologue and epilogue, one 32-key tile, the combine launch with the float32
-// epilogue it needs, one partial written and merged; and the workgroups an XCD
-// holds at once (32 compute units; the LDS leaves the 64-head kernel one each).
+// at the warm clock, fitted to steps with forced plans): a workgroup's prologue
+// and epilogue and one 32-key tile, with all heads and with half of them (64
+// heads only), the combine launch with the float32 epilogue it needs, one
+// partial written and merged; and the workgroups an XCD holds at once (32
+// compute units; the LDS leaves the 64-head kernel one each).
 struct SplitCost {
-  float fixed, tile, combine, partial;
+  float fixed[2], tile[2], combine, partial;
   int slots;
 };
 static SplitCost split_cost(const tv_dims &d) {
-  return d.H == 64 ? SplitCost{8.0f, 0.8f, 5.0f, 0.03f, 32} : SplitCost{6.0f, 0.65f, 4.0f, 0.002f, 64};
+  return d.H == 64 ? SplitCost{{8.0f, 7.0f}, {0.8f, 0.55f}, 5.0f, 0.03f, 32}
+                   : SplitCost{{6.0f, 6.0f}, {0.65f, 0.65f}, 4.0f, 0.002f, 64};
 }
 
-static SplitPlan plan_of(int64_t mk, int64_t splits) {
+static SplitPlan plan_of(int64_t mk, int64_t splits, int halves = 1) {
   SplitPlan p;
   const int64_t chunk = ((mk + splits - 1) / splits + 31) / 32 * 32;
   p.max_keys = (int32_t)mk;
   p.chunk = (int32_t)chunk;
   p.splits = (int32_t)((mk + chunk - 1) / chunk);
+  p.halves = halves;
   return p;
 }
 
-// The cheapest split count by the cost above: the fewest the pointer table
-// allows, or one of those with which all workgroups still run at once (one
-// more round of workgroups costs more than any split saves).  An XCD gets whole
-// rows when there are 8 or more (unit_of), so the fullest XCD decides: 12 rows
-// of 7 nodes fill 14 of its 32 compute units unsplit and need two rounds in
-// three splits (step 55.5 us unsplit, 58.0 in two, 68.1 in three).  Measured
-// otherwise, 64 heads, splits: step in us (712 keys): 8 nodes 1: 42.2, 2: 37.9,
-// 4: 33.8, 8: 33.0, 12: 34.6; 128 nodes 1: 49.7, 2: 54.1; 160 nodes 1: 51.7,
-// 2: 74.3 (two rounds); 192 nodes of 32 a row 1: 89.1, 2: 115.3.  8 heads: 8
-// nodes of 776 keys 1: 38.1, 3: 30.2, 8: 26.7; 222 nodes of 404 keys 1: 39.4,
-// 2: 40.9.
+// The cheapest plan by the cost above: a workgroup or two (half the heads each,
+// no partials to merge) per split, and the fewest splits the pointer table
+// allows or as many as still run at once (one more round of workgroups costs
+// more than any plan saves).  An XCD gets whole rows when there are 8 or more
+// (unit_of), so the fullest XCD decides: 12 rows of 7 nodes fill 14 of its 32
+// compute units whole and need two rounds in three splits.  Measured, 64 heads,
+// about 712 keys, steps in us by splits (h: in halves): 8 nodes 1: 41.0, 4: 34.7,
+// 8: 33.7, h1: 35.3, h4: 31.1, h12: 34.5; 48 nodes 1: 42.4, 2: 45.9, 4: 41.8,
+// h1: 36.1, h2: 40.9; 84 paged nodes 1: 47.8, 2: 51.0, 4: 60.9, h1: 41.0; 128
+// nodes 1: 48.3, 2: 53.0, h1: 42.4; 160 nodes (h1: two rounds) 1: 50.9, 2: 74.3,
+// h1: 61.5; 192 nodes, 32 a row, 1: 57.6, 2: 83.8, h1: 68.3.  8 heads: 8 nodes of
+// 776 keys 1: 38.1, 3: 30.2, 8: 26.7; 222 nodes of 404 keys 1: 39.4, 2: 40.9.
 SplitPlan split_plan(const tv_dims &d) {
   const SplitCost k = split_cost(d);
   const int64_t mk = (int64_t)d.topk + d.max_len / d.ratio_hca + d.D + d.window;
   const int64_t nodes = (int64_t)d.B * d.D;
-  auto per_xcd = [&](int64_t splits) {
-    if (d.B >= 8) return (int64_t)((d.B + 7) / 8) * d.D * splits;
-    return (nodes * attn_padded_splits(d.B, (int)splits) + 7) / 8;
+  auto per_xcd = [&](int64_t splits, int halves) {
+    if (d.B >= 8) return (int64_t)((d.B + 7) / 8) * d.D * halves * splits;
+    return (nodes * halves * attn_padded_splits(d.B, (int)splits) + 7) / 8;
   };
   auto cost = [&](const SplitPlan &p) {
-    const int64_t rounds = (per_xcd(p.splits) + k.slots - 1) / k.slots;
-    return (float)rounds * (k.fixed + k.tile * (float)(p.chunk / 32)) +
+    const int64_t rounds = (per_xcd(p.splits, p.halves) + k.slots - 1) / k.slots;
+    return (float)rounds * (k.fixed[p.halves - 1] + k.tile[p.halves - 1] * (float)(p.chunk / 32)) +
            (p.splits > 1 ? k.combine + k.partial * (float)(nodes * p.splits) : 0.0f);
   };
   const int64_t least = (mk + kAttnMaxChunk - 1) / kAttnMaxChunk;  // pointer table bound
   SplitPlan best = plan_of(mk, least);
   float best_cost = cost(best);
-  for (int64_t s = least + 1; s <= (mk + 31) / 32 && per_xcd(s) <= k.slots; ++s) {
-    const SplitPlan p = plan_of(mk, s);
-    const float c = cost(p);
-    if (c < best_cost) {
-      best = p;
-      best_cost = c;
+  for (int halves = 1; halves <= (d.H == 64 ? 2 : 1); ++halves)
+    for (int64_t s = least; s <= (mk + 31) / 32 && per_xcd(s, halves) <= k.slots; ++s) {
+      const SplitPlan p = plan_of(mk, s, halves);
+      const float c = cost(p);
+      if (c < best_cost) {
+        best = p;
+        best_cost = c;
+      }
     }
-  }
   return best;
 }
 
@@ -188,7 +193,7 @@ WsLayout ws_layout(const tv_dims &d) {
   const int64_t mk = w.plan.max_keys;
   const int64_t least = (mk + kAttnMaxChunk - 1) / kAttnMaxChunk;
   if (w.total <= TV_NOALLOC_SCRATCH_BYTES || w.plan.splits <= least) return w;
-  const WsLayout fewest = ws_layout_of(d, plan_of(mk, least));
+  const WsLayout fewest = ws_layout_of(d, plan_of(mk, least, w.plan.halves));
   return fewest.total <= TV_NOALLOC_SCRATCH_BYTES ? fewest : w;
 }
 

@@ -40,6 +40,7 @@ namespace tv {
 namespace mla {
 
 constexpr int kH = 64, kDK = 576, kDV = 512;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 constexpr int kNW = 8, kNT = kNW * 64;
 constexpr int kKS = kDK / 16;             // logit k-steps of 16 channels
 constexpr int kGroups = kDK / 64;         // 128-byte column groups of a row (the last one: rope channels)
@@ -107,21 +108,36 @@ __device__ __forceinline__ void vm_wait_n(int n) {
   }
 }
 
+// HW: query heads of a workgroup, all 64, or 32 of them (two workgroups take a
+// split) where the grid would leave compute units idle.  What bounds a tile is
+// the logit waves' serial chain, so with 32 heads they share a tile by keys
+// instead of heads, 16 each on 16x16x32 products: 36 products and eight
+// exponentials a lane instead of 36 larger ones and sixteen, every key row read
+// once by them, the value waves at half their products.  128 nodes of about 770
+// keys: 33.7 us with 128 workgroups, 26 with 256 of half the heads (a tile 1.07
+// and 0.7 us).
+template <int HW>
 __global__ void __launch_bounds__(mla::kNT, 1)
 attn_mla_kernel(tv_dims d, const uint16_t *__restrict__ q, const int32_t *__restrict__ row_status,
                 const int32_t *__restrict__ row_order, const uint16_t *const *__restrict__ keytab, int keytab_stride,
                 const int32_t *__restrict__ nkeys_tab, int chunk, int splits, float *__restrict__ part_o,
                 float *__restrict__ part_ml, uint16_t *__restrict__ out, float *__restrict__ lse) {
   using namespace mla;
+  static_assert(HW == 64 || HW == 32, "whole 32-head tiles");
+  constexpr int kHT = HW / 32;       // head tiles of a value wave
+  constexpr int kHalves = kH / HW;   // workgroups that share a node's heads
   __shared__ __attribute__((aligned(1024))) unsigned char sK[kNBUF][kTB];
-  __shared__ __attribute__((aligned(16))) unsigned char sP[2][kH * 64];
+  __shared__ __attribute__((aligned(16))) unsigned char sP[2][HW * 64];
   __shared__ __attribute__((aligned(16))) const uint16_t *sPtr[kPSlots][kKT];
   __shared__ int sOver[2];
-  __shared__ float sSum[kH];
+  __shared__ float sSum[HW];
+  __shared__ float sSeen[2][HW == 32 ? 32 : 1];  // 32 heads: the largest logits of either key half
 
   int i, split;
-  const int rank = unit_of(blockIdx.x, d.B, d.D, splits, i, split);
+  const int rank = unit_of(blockIdx.x, d.B, d.D * kHalves, splits, i, split);
   if (rank >= d.B) return;
+  const int h0 = HW * (i % kHalves);  // first head; a node's halves are neighbours in the grid
+  i /= kHalves;
   const int64_t rnode = (int64_t)rank * d.D + i;  // key table and key count are kept by (rank, node)
   const int b = row_order[rank];
   const int64_t node = (int64_t)b * d.D + i;
@@ -218,103 +234,225 @@ attn_mla_kernel(tv_dims d, const uint16_t *__restrict__ q, const int32_t *__rest
   };
 
   if (wv == 0 || wv == 1) {
-    // ---- logit wave: heads 32 hh .. 32 hh + 31 ------------------------------
-    const int hh = wv;
-    const int head = 32 * hh + l32;
-    // Queries as the B operand: lane holds head `head`, channels 16 ks + 8 hi .. +7.
-    bf16x8 qf[kKS];
-    {
-      const uint16_t *qrow = q + (node * kH + head) * kDK + 8 * hi;
+    if constexpr (HW == 64) {
+      // ---- logit wave: heads 32 hh .. 32 hh + 31 ------------------------------
+      const int hh = wv;
+      const int head = 32 * hh + l32;
+      // Queries as the B operand: lane holds head `head`, channels 16 ks + 8 hi .. +7.
+      bf16x8 qf[kKS];
+      {
+        const uint16_t *qrow = q + (node * kH + head) * kDK + 8 * hi;
 #pragma unroll
-      for (int ks = 0; ks < kKS; ++ks)
-        qf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(qrow + 16 * ks));
-    }
-    // A operand: lane reads row l32, chunk 2 (ks & 3) + hi of group ks / 4.
-    int kofs[4];
+        for (int ks = 0; ks < kKS; ++ks)
+          qf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(qrow + 16 * ks));
+      }
+      // A operand: lane reads row l32, chunk 2 (ks & 3) + hi of group ks / 4.
+      int kofs[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) kofs[c] = l32 * 128 + slot(l32, 2 * c + hi) * 16;
-    const int pw0 = p_off(head, hi), pw1 = p_off(head, 2 + hi);
+      for (int c = 0; c < 4; ++c) kofs[c] = l32 * 128 + slot(l32, 2 * c + hi) * 16;
+      const int pw0 = p_off(head, hi), pw1 = p_off(head, 2 + hi);
 
-    float m_ref = -INFINITY, m_seen = -INFINITY;
-    // Complete logits of the tile's 32 keys x this wave's 32 heads: two
-    // accumulator chains (even and odd k-steps), key reads six ahead.
-    auto qk_tile = [&](int tile) {
-      const unsigned char *kt = sK[tile % kNBUF];
-      f32x16 s0 = f32x16{}, s1 = f32x16{};
+      float m_ref = -INFINITY, m_seen = -INFINITY;
+      // Complete logits of the tile's 32 keys x this wave's 32 heads: two
+      // accumulator chains (even and odd k-steps), key reads six ahead.
+      auto qk_tile = [&](int tile) {
+        const unsigned char *kt = sK[tile % kNBUF];
+        f32x16 s0 = f32x16{}, s1 = f32x16{};
 #pragma unroll
-      for (int ks = 0; ks < kKS; ++ks) {
-        const bf16x8 a = *reinterpret_cast<const bf16x8 *>(kt + (ks >> 2) * kGB + kofs[ks & 3]);
-        if (ks & 1)
-          s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], s1, 0, 0, 0);
-        else
-          s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], s0, 0, 0, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+        for (int ks = 0; ks < kKS; ++ks) {
+          const bf16x8 a = *reinterpret_cast<const bf16x8 *>(kt + (ks >> 2) * kGB + kofs[ks & 3]);
+          if (ks & 1)
+            s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], s1, 0, 0, 0);
+          else
+            s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[ks], s0, 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
 #pragma unroll
-      for (int r = 0; r < kKS - 6; ++r) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
-      return s0 + s1;
-    };
-    // Element v of a lane's logits is key 8 (v / 4) + 4 hi + v % 4 of the
-    // tile; keys past the split are -inf.  Probabilities against the reference
-    // go to LDS as bf16 P^T; their sums come from the value contraction.
-    auto process = [&](int tile, f32x16 s, bool first) {
-      const int nvalid = nkeys - tile * kKT;
-      if (nvalid < kKT) {
+        for (int r = 0; r < kKS - 6; ++r) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
+        return s0 + s1;
+      };
+      // Element v of a lane's logits is key 8 (v / 4) + 4 hi + v % 4 of the
+      // tile; keys past the split are -inf.  Probabilities against the reference
+      // go to LDS as bf16 P^T; their sums come from the value contraction.
+      auto process = [&](int tile, f32x16 s, bool first) {
+        const int nvalid = nkeys - tile * kKT;
+        if (nvalid < kKT) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
-          if (8 * (v >> 2) + 4 * hi + (v & 3) >= nvalid) s[v] = -INFINITY;
-      }
-      float mx = s[0];
+          for (int v = 0; v < 16; ++v)
+            if (8 * (v >> 2) + 4 * hi + (v & 3) >= nvalid) s[v] = -INFINITY;
+        }
+        float mx = s[0];
 #pragma unroll
-      for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
-      mx *= sl2;
-      if (first) m_ref = fmaxf(mx, __shfl_xor(mx, 32, 64));  // the reference: the first tile's maximum
-      m_seen = fmaxf(m_seen, mx);
-      float p[16];
+        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
+        mx *= sl2;
+        if (first) m_ref = fmaxf(mx, __shfl_xor(mx, 32, 64));  // the reference: the first tile's maximum
+        m_seen = fmaxf(m_seen, mx);
+        float p[16];
 #pragma unroll
-      for (int v = 0; v < 16; ++v) p[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[v], sl2, -m_ref));
-      uint4 c0, c1;
-      c0.x = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p[0], p[1]}, bf16x2));
-      c0.y = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p[2], p[3]}, bf16x2));
-      c0.z = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p[4], p[5]}, bf16x2));
-      c0.w = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p[6], p[7]}, bf16x2));
-      c1.x = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p[8], p[9]}, bf16x2));
-      c1.y = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p[10], p[11]}, bf16x2));
-      c1.z = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p[12], p[13]}, bf16x2));
-      c1.w = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p[14], p[15]}, bf16x2));
-      unsigned char *pt = sP[tile & 1];
-      *reinterpret_cast<uint4 *>(pt + pw0) = c0;
-      *reinterpret_cast<uint4 *>(pt + pw1) = c1;
-    };
+        for (int v = 0; v < 16; ++v) p[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[v], sl2, -m_ref));
+        uint4 c0, c1;
+        c0.x = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p[0], p[1]}, bf16x2));
+        c0.y = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p[2], p[3]}, bf16x2));
+        c0.z = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p[4], p[5]}, bf16x2));
+        c0.w = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p[6], p[7]}, bf16x2));
+        c1.x = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p[8], p[9]}, bf16x2));
+        c1.y = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p[10], p[11]}, bf16x2));
+        c1.z = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p[12], p[13]}, bf16x2));
+        c1.w = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p[14], p[15]}, bf16x2));
+        unsigned char *pt = sP[tile & 1];
+        *reinterpret_cast<uint4 *>(pt + pw0) = c0;
+        *reinterpret_cast<uint4 *>(pt + pw1) = c1;
+      };
 
-    for (int attempt = 0;; ++attempt) {
-      lds_barrier();  // pointer tables of the first tiles copied
-      __builtin_amdgcn_s_waitcnt(0x0F70);  // queries are in registers
-      lds_barrier();  // tile 0 landed
-      for (int it = -1; it < T; ++it) {
-        if (it + 1 < T) process(it + 1, qk_tile(it + 1), it + 1 == 0 && attempt == 0);
-        if (it == T - 1) break;
+      for (int attempt = 0;; ++attempt) {
+        lds_barrier();  // pointer tables of the first tiles copied
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // queries are in registers
+        lds_barrier();  // tile 0 landed
+        for (int it = -1; it < T; ++it) {
+          if (it + 1 < T) process(it + 1, qk_tile(it + 1), it + 1 == 0 && attempt == 0);
+          if (it == T - 1) break;
+          lds_barrier();
+        }
+        const float seen = fmaxf(m_seen, __shfl_xor(m_seen, 32, 64));
+        const bool over = __any(seen > m_ref + kSlack);
+        if (lane == 0) sOver[hh] = over ? 1 : 0;
+        lds_barrier();  // E: the overflow verdicts and the sums are published
+        if (!restart_now(attempt)) break;
+        m_ref = seen;  // restart from the largest logit seen
         lds_barrier();
       }
-      const float seen = fmaxf(m_seen, __shfl_xor(m_seen, 32, 64));
-      const bool over = __any(seen > m_ref + kSlack);
-      if (lane == 0) sOver[hh] = over ? 1 : 0;
-      lds_barrier();  // E: the overflow verdicts and the sums are published
-      if (!restart_now(attempt)) break;
-      m_ref = seen;  // restart from the largest logit seen
-      lds_barrier();
-    }
-    if (hi == 0) {
-      const float lsum = sSum[head];
-      if (single) {
-        if (lse) lse[node * kH + head] = (m_ref + __log2f(lsum)) * kLn2;
-      } else {
-        part_ml[(((node * splits) + split) * kH + head) * 2 + 0] = m_ref;
-        part_ml[(((node * splits) + split) * kH + head) * 2 + 1] = lsum;
+      if (hi == 0) {
+        const float lsum = sSum[head];
+        if (single) {
+          if (lse) lse[node * kH + head] = (m_ref + __log2f(lsum)) * kLn2;
+        } else {
+          part_ml[(((node * splits) + split) * kH + head) * 2 + 0] = m_ref;
+          part_ml[(((node * splits) + split) * kH + head) * 2 + 1] = lsum;
+        }
+      }
+    } else {
+      // ---- logit wave: keys 16 wv .. 16 wv + 15 of a tile, 32 heads -----------
+      // S^T = K Q^T on 16x16x32 products, two head tiles, two accumulator
+      // chains each.  Both waves measure their logits against one reference
+      // per head: the maximum over the first tile's first 16 keys, which both
+      // compute.
+      const int l16 = lane & 15, g = lane >> 4;
+      constexpr int kKS2 = kDK / 32;  // k-steps of 32 channels
+      bf16x8 qf[2][kKS2];             // lane: head 16 t + l16, channels 32 ks + 8 g .. +7
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const uint16_t *qrow = q + (node * kH + h0 + 16 * t + l16) * kDK + 8 * g;
+#pragma unroll
+        for (int ks = 0; ks < kKS2; ++ks)
+          qf[t][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(qrow + 32 * ks));
+      }
+      // A operand: lane reads key row 16 kw + l16, chunk 4 (ks & 1) + g of group ks / 2 (the slot depends on
+      // the row's low four bits only, so a wave's rows are a fixed 2,048 bytes apart)
+      int kofs[2];
+#pragma unroll
+      for (int c = 0; c < 2; ++c) kofs[c] = l16 * 128 + slot(l16, 4 * c + g) * 16;
+      // keys 16 wv + 4 g .. + 3 of a head: half of the head's chunk 2 wv + (g & 1)
+      int pw[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) pw[t] = p_off(16 * t + l16, 2 * wv + (g & 1)) + 8 * (g >> 1);
+      float m_ref[2] = {-INFINITY, -INFINITY}, m_seen[2] = {-INFINITY, -INFINITY};
+      f32x4 sc[2];  // lane: heads 16 t + l16, keys 16 kw + 4 g + 0..3
+      auto qk_tile = [&](int tile, int kw) {
+        const unsigned char *kt = sK[tile % kNBUF] + kw * 2048;
+        f32x4 acc[2][2] = {};
+#pragma unroll
+        for (int ks = 0; ks < kKS2; ++ks) {
+          const bf16x8 a = *reinterpret_cast<const bf16x8 *>(kt + (ks >> 1) * kGB + kofs[ks & 1]);
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+            acc[t][ks & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qf[t][ks], acc[t][ks & 1], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+#pragma unroll
+        for (int r = 0; r < kKS2 - 6; ++r) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, 12, 0);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) sc[t] = acc[t][0] + acc[t][1];
+        const int nvalid = nkeys - tile * kKT - 16 * kw - 4 * g;  // keys past the split are -inf
+        if (nkeys - tile * kKT < kKT)
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              if (v >= nvalid) sc[t][v] = -INFINITY;
+      };
+      auto tile_max = [&](int t) { return fmaxf(fmaxf(sc[t][0], sc[t][1]), fmaxf(sc[t][2], sc[t][3])) * sl2; };
+      auto head_max = [&](float x) {  // over the lanes of a head
+        x = fmaxf(x, __shfl_xor(x, 16, 64));
+        return fmaxf(x, __shfl_xor(x, 32, 64));
+      };
+      auto publish = [&](int tile) {
+        unsigned char *pt = sP[tile & 1];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          m_seen[t] = fmaxf(m_seen[t], tile_max(t));
+          float p[4];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) p[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[t][v], sl2, -m_ref[t]));
+          uint2 c;
+          c.x = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p[0], p[1]}, bf16x2));
+          c.y = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){p[2], p[3]}, bf16x2));
+          *reinterpret_cast<uint2 *>(pt + pw[t]) = c;
+        }
+      };
+      for (int attempt = 0;; ++attempt) {
+        lds_barrier();  // pointer tables of the first tiles copied
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // queries are in registers
+        lds_barrier();  // tile 0 landed
+        for (int it = -1; it < T; ++it) {
+          if (it == -1 && attempt == 0) {  // the reference
+            qk_tile(0, 0);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) m_ref[t] = head_max(tile_max(t));
+            if (wv != 0) qk_tile(0, 1);
+            publish(0);
+          } else if (it + 1 < T) {
+            qk_tile(it + 1, wv);
+            publish(it + 1);
+          }
+          if (it == T - 1) break;
+          lds_barrier();
+        }
+        bool over = false;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const float seen = head_max(m_seen[t]);
+          over |= seen > m_ref[t] + kSlack;
+          if (g == 0) sSeen[wv][16 * t + l16] = seen;
+        }
+        const bool any = __any(over);
+        if (lane == 0) sOver[wv] = any ? 1 : 0;
+        lds_barrier();  // E: the overflow verdicts, the largest logits and the sums are published
+        if (!restart_now(attempt)) break;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)  // restart from the largest logit seen
+          m_ref[t] = fmaxf(sSeen[0][16 * t + l16], sSeen[1][16 * t + l16]);
+        lds_barrier();
+      }
+      if (wv == 0 && g == 0) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const int head = 16 * t + l16;
+          const float lsum = sSum[head];
+          if (single) {
+            if (lse) lse[node * kH + h0 + head] = (m_ref[t] + __log2f(lsum)) * kLn2;
+          } else {
+            part_ml[(((node * splits) + split) * kH + h0 + head) * 2 + 0] = m_ref[t];
+            part_ml[(((node * splits) + split) * kH + h0 + head) * 2 + 1] = lsum;
+          }
+        }
       }
     }
   } else if (wv == 4 || wv == 5) {
@@ -349,15 +487,15 @@ attn_mla_kernel(tv_dims d, const uint16_t *__restrict__ q, const int32_t *__rest
         voff[rr][ct] = off(16 * (rr >> 1) + 8 * (rr & 1) + 4 * hi + (jj >> 2),
                            128 * pq + 32 * ct + 16 * (g & 1) + 4 * (jj & 3));
     const bf16x8 ones = __builtin_bit_cast(bf16x8, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
-    f32x16 acc_o[2][4], acc_l[2];
+    f32x16 acc_o[kHT][4], acc_l[kHT];
     auto pv_tile = [&](int it) {
       const unsigned char *kt = sK[it % kNBUF];
       const unsigned char *pt = sP[it & 1];
-      bf16x8 pb[2][2];
+      bf16x8 pb[2][kHT];
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-        for (int t = 0; t < 2; ++t) pb[ks][t] = *reinterpret_cast<const bf16x8 *>(pt + p_off(32 * t + l32, 2 * ks + hi));
+        for (int t = 0; t < kHT; ++t) pb[ks][t] = *reinterpret_cast<const bf16x8 *>(pt + p_off(32 * t + l32, 2 * ks + hi));
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
 #pragma unroll
@@ -367,18 +505,18 @@ attn_mla_kernel(tv_dims d, const uint16_t *__restrict__ q, const int32_t *__rest
           const bf16x8 va = __builtin_bit_cast(bf16x8, (short __attribute__((ext_vector_type(8)))){
                                                            v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]});
 #pragma unroll
-          for (int t = 0; t < 2; ++t)
+          for (int t = 0; t < kHT; ++t)
             acc_o[t][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[ks][t], acc_o[t][ct], 0, 0, 0);
         }
         if (pq == 0)
 #pragma unroll
-          for (int t = 0; t < 2; ++t) acc_l[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, pb[ks][t], acc_l[t], 0, 0, 0);
+          for (int t = 0; t < kHT; ++t) acc_l[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, pb[ks][t], acc_l[t], 0, 0, 0);
       }
     };
 
     for (int attempt = 0;; ++attempt) {
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
+      for (int t = 0; t < kHT; ++t) {
         acc_l[t] = f32x16{};
 #pragma unroll
         for (int ct = 0; ct < 4; ++ct) acc_o[t][ct] = f32x16{};
@@ -396,8 +534,8 @@ attn_mla_kernel(tv_dims d, const uint16_t *__restrict__ q, const int32_t *__rest
       }
       vm_wait<0>();
       if (pq == 0 && hi == 0) {  // every row of the sums' accumulator holds the sum of its lane's head
-        sSum[l32] = acc_l[0][0];
-        sSum[32 + l32] = acc_l[1][0];
+#pragma unroll
+        for (int t = 0; t < kHT; ++t) sSum[32 * t + l32] = acc_l[t][0];
       }
       lds_barrier();  // E
       if (!restart_now(attempt)) break;
@@ -408,9 +546,9 @@ attn_mla_kernel(tv_dims d, const uint16_t *__restrict__ q, const int32_t *__rest
     // 4 hi + (j % 4).  The wave writes its block as rows [head][128 channels]
     // (bf16, 256-byte rows; float32, 512-byte rows for a split's partial),
     // 16-byte chunks XOR-swizzled by head, then stores each row contiguously.
-    unsigned char *ob = &sK[0][0] + pq * (single ? 64 * 256 : 64 * 512);
+    unsigned char *ob = &sK[0][0] + pq * (single ? HW * 256 : HW * 512);
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; t < kHT; ++t) {
       const int h = t * 32 + l32;
       const float inv = single ? 1.0f / sSum[h] : 1.0f;
 #pragma unroll
@@ -432,17 +570,17 @@ attn_mla_kernel(tv_dims d, const uint16_t *__restrict__ q, const int32_t *__rest
     }
     if (single) {
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {  // rows 4u .. 4u+3, sixteen 16-byte chunks each
+      for (int u = 0; u < HW / 4; ++u) {  // rows 4u .. 4u+3, sixteen 16-byte chunks each
         const int r = 4 * u + (lane >> 4), ch = lane & 15;
         const uint4 v = *reinterpret_cast<const uint4 *>(ob + r * 256 + ((ch ^ (r & 15)) << 4));
-        *reinterpret_cast<uint4 *>(out + (node * kH + r) * kDV + 128 * pq + 8 * ch) = v;
+        *reinterpret_cast<uint4 *>(out + (node * kH + h0 + r) * kDV + 128 * pq + 8 * ch) = v;
       }
     } else {
 #pragma unroll
-      for (int u = 0; u < 32; ++u) {  // rows 2u, 2u+1, thirty-two 16-byte chunks each
+      for (int u = 0; u < HW / 2; ++u) {  // rows 2u, 2u+1, thirty-two 16-byte chunks each
         const int r = 2 * u + (lane >> 5), ch = lane & 31;
         const float4 v = *reinterpret_cast<const float4 *>(ob + r * 512 + ((ch ^ (r & 31)) << 4));
-        *reinterpret_cast<float4 *>(part_o + (((node * splits) + split) * kH + r) * kDV + 128 * pq + 4 * ch) = v;
+        *reinterpret_cast<float4 *>(part_o + (((node * splits) + split) * kH + h0 + r) * kDV + 128 * pq + 4 * ch) = v;
       }
     }
   }
@@ -455,8 +593,11 @@ hipError_t launch_attn_mla(const tv_dims &d, const uint16_t *q, const int32_t *r
       d.d_row != mla::kDK)
     return hipErrorInvalidValue;
   const int64_t grid = attn_grid(d, plan);
-  attn_mla_kernel<<<dim3((unsigned)grid), mla::kNT, 0, s>>>(d, q, row_status, row_order, keytab, plan.max_keys, nkeys,
-                                                           plan.chunk, plan.splits, part_o, part_ml, out, lse);
+  auto go = [&](auto kernel) {
+    kernel<<<dim3((unsigned)grid), mla::kNT, 0, s>>>(d, q, row_status, row_order, keytab, plan.max_keys, nkeys,
+                                                     plan.chunk, plan.splits, part_o, part_ml, out, lse);
+  };
+  plan.halves == 2 ? go(attn_mla_kernel<32>) : go(attn_mla_kernel<64>);
   return hipGetLastError();
 }
 

@@ -36,6 +36,7 @@ struct SplitPlan {
   int32_t max_keys;   // upper bound of any node's key count
   int32_t chunk;      // keys per split (multiple of the key tile)
   int32_t splits;     // splits per node
+  int32_t halves;     // workgroups that share a split's heads: 1, or 2 (64 heads only)
 };
 
 // Byte offsets of the verify workspace regions.
@@ -74,8 +75,8 @@ __host__ __device__ inline int attn_padded_splits(int B, int splits) {
 }
 // Workgroups of the attention grid (see unit_of).
 inline int64_t attn_grid(const tv_dims &d, const SplitPlan &p) {
-  if (d.B < 8) return (int64_t)d.B * d.D * attn_padded_splits(d.B, p.splits);
-  return (int64_t)((d.B + 7) / 8) * 8 * d.D * p.splits;
+  if (d.B < 8) return (int64_t)d.B * d.D * p.halves * attn_padded_splits(d.B, p.splits);
+  return (int64_t)((d.B + 7) / 8) * 8 * d.D * p.halves * p.splits;
 }
 WsLayout ws_layout(const tv_dims &d);
 
