@@ -35,6 +35,9 @@ typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 // positions in every node's list, which past the CSA selections are the same
 // HCA entries, so those stay in one L2.  Padding units return at once.
 //
+// Where two workgroups share a split's heads, D counts both for every node:
+// i / 2 is the node, i % 2 its half.
+//
 // Returns the rank; the unit is valid when the rank is below B.
 __device__ __forceinline__ int unit_of(int blk, int B, int D, int splits, int &i, int &s) {
   if (B < 8) {

@@ -2,7 +2,8 @@
 // over one 576-wide latent row per key; keys are the whole row, values its
 // first 512 channels.
 //
-// One workgroup (8 wavefronts) takes one (row, node, key split).  Wavefronts
+// One workgroup (8 wavefronts) takes one (row, node, key split), with all 64
+// heads (described here) or with half of them (HW = 32, below).  Wavefronts
 // w and w+4 share a SIMD, and w0..w3 occupy the four SIMDs, so the roles are:
 //   w0, w1  logit waves: S^T = K Q^T for 32 keys x 32 heads (head half w)
 //           over all 576 channels on v_mfma_f32_32x32x16_bf16, the queries of
