@@ -45,3 +45,23 @@ def test_topk_edges(kind, topk):
     torch.cuda.synchronize()
     s2 = r2.host("sel")
     assert np.mean(sel != s2) < 0.01  # its own scratch: near ties only
+
+
+@pytest.mark.parametrize("topk", [33, 2047])
+def test_merge_across_zero(topk):
+    """Segmented nodes whose scores straddle zero, many of them exactly zero:
+    the survivors' distances span most of the 32 bits (the merge's wide first
+    digit) and the threshold is a tie."""
+    from paper_2609_24698_amd import DeviceRound
+
+    w = synth.make_workload("C0", seed=340 + topk, B=2, D=3, lens=[4 * 33800 + 1, 4 * 17000], tree="random", topk=topk)
+    w.w_idx[:, :, 1:] |= 0x8000  # head 0 alone can raise a score
+    w.w_idx[:, :, 0] &= 0x7FFF
+    nodes = [(b, i) for b in range(w.B) for i in range(w.D)]
+    ref = O.run_round(w, nodes)
+
+    def rerun(b, i, chosen):
+        return O.verify_node(w, b, i, ref["anc"], ref["depth"], ref["scr_c4"], ref["scr_c128"], chosen=chosen)
+
+    print("topk", topk, flush=True)
+    _check_stages(w, ref, DeviceRound(w, "cuda:0"), nodes, rerun=rerun)
