@@ -98,15 +98,21 @@ static SplitCost split_cost(const tv_dims &d) {
                    : SplitCost{{6.0f, 6.0f}, {0.65f, 0.65f}, 4.0f, 0.002f, 64};
 }
 
-static SplitPlan plan_of(int64_t mk, int64_t splits, int halves = 1) {
+// The plan of chunks of ct 32-key tiles, among `tiles` of them.
+static SplitPlan plan_of(int64_t mk, int32_t tiles, int32_t ct, int halves) {
   SplitPlan p;
-  const int64_t chunk = ((mk + splits - 1) / splits + 31) / 32 * 32;
   p.max_keys = (int32_t)mk;
-  p.chunk = (int32_t)chunk;
-  p.splits = (int32_t)((mk + chunk - 1) / chunk);
+  p.chunk = 32 * ct;
+  p.splits = (tiles + ct - 1) / ct;
   p.halves = halves;
   return p;
 }
+
+static int64_t max_keys_of(const tv_dims &d) {
+  return (int64_t)d.topk + d.max_len / d.ratio_hca + d.D + d.window;
+}
+// The fewest splits, by the pointer table's bound.
+static int32_t least_splits(int64_t mk) { return (int32_t)((mk + kAttnMaxChunk - 1) / kAttnMaxChunk); }
 
 // The cheapest plan by the cost above: a workgroup or two (half the heads each,
 // no partials to merge) per split, and the fewest splits the pointer table
@@ -120,30 +126,33 @@ static SplitPlan plan_of(int64_t mk, int64_t splits, int halves = 1) {
 // nodes 1: 48.3, 2: 53.0, h1: 42.4; 160 nodes (h1: two rounds) 1: 50.9, 2: 74.3,
 // h1: 61.5; 192 nodes, 32 a row, 1: 57.6, 2: 83.8, h1: 68.3.  8 heads: 8 nodes of
 // 776 keys 1: 38.1, 3: 30.2, 8: 26.7; 222 nodes of 404 keys 1: 39.4, 2: 40.9.
+// Every call makes its plan anew, so the search steps over the chunk sizes that
+// differ, not over all split counts.
 SplitPlan split_plan(const tv_dims &d) {
   const SplitCost k = split_cost(d);
-  const int64_t mk = (int64_t)d.topk + d.max_len / d.ratio_hca + d.D + d.window;
+  const int64_t mk = max_keys_of(d);
+  const int32_t tiles = (int32_t)((mk + 31) / 32), least = least_splits(mk);
   const int64_t nodes = (int64_t)d.B * d.D;
-  auto per_xcd = [&](int64_t splits, int halves) {
+  auto per_xcd = [&](int32_t splits, int halves) {
     if (d.B >= 8) return (int64_t)((d.B + 7) / 8) * d.D * halves * splits;
-    return (nodes * halves * attn_padded_splits(d.B, (int)splits) + 7) / 8;
+    return (nodes * halves * attn_padded_splits(d.B, splits) + 7) / 8;
   };
-  auto cost = [&](const SplitPlan &p) {
-    const int64_t rounds = (per_xcd(p.splits, p.halves) + k.slots - 1) / k.slots;
-    return (float)rounds * (k.fixed[p.halves - 1] + k.tile[p.halves - 1] * (float)(p.chunk / 32)) +
-           (p.splits > 1 ? k.combine + k.partial * (float)(nodes * p.splits) : 0.0f);
-  };
-  const int64_t least = (mk + kAttnMaxChunk - 1) / kAttnMaxChunk;  // pointer table bound
-  SplitPlan best = plan_of(mk, least);
-  float best_cost = cost(best);
+  SplitPlan best{};
+  float best_cost = INFINITY;
   for (int halves = 1; halves <= (d.H == 64 ? 2 : 1); ++halves)
-    for (int64_t s = least; s <= (mk + 31) / 32 && per_xcd(s, halves) <= k.slots; ++s) {
-      const SplitPlan p = plan_of(mk, s, halves);
-      const float c = cost(p);
+    for (int32_t s = least; s <= tiles;) {
+      const int32_t ct = (tiles + s - 1) / s;
+      const SplitPlan p = plan_of(mk, tiles, ct, halves);
+      const int64_t wgs = per_xcd(p.splits, halves);
+      const bool first = halves == 1 && s == least;  // always possible, in as many rounds as it takes
+      if (!first && wgs > k.slots) break;
+      const float c = (float)((wgs + k.slots - 1) / k.slots) * (k.fixed[halves - 1] + k.tile[halves - 1] * (float)ct) +
+                      (p.splits > 1 ? k.combine + k.partial * (float)(nodes * p.splits) : 0.0f);
       if (c < best_cost) {
         best = p;
         best_cost = c;
       }
+      s = p.splits + 1;
     }
   return best;
 }
@@ -190,10 +199,10 @@ static WsLayout ws_layout_of(const tv_dims &d, const SplitPlan &plan) {
 // the fewest splits fit it, is not worth that entry's refusal.
 WsLayout ws_layout(const tv_dims &d) {
   const WsLayout w = ws_layout_of(d, split_plan(d));
+  if (w.total <= TV_NOALLOC_SCRATCH_BYTES) return w;
   const int64_t mk = w.plan.max_keys;
-  const int64_t least = (mk + kAttnMaxChunk - 1) / kAttnMaxChunk;
-  if (w.total <= TV_NOALLOC_SCRATCH_BYTES || w.plan.splits <= least) return w;
-  const WsLayout fewest = ws_layout_of(d, plan_of(mk, least, w.plan.halves));
+  const int32_t tiles = (int32_t)((mk + 31) / 32), least = least_splits(mk);
+  const WsLayout fewest = ws_layout_of(d, plan_of(mk, tiles, (tiles + least - 1) / least, w.plan.halves));
   return fewest.total <= TV_NOALLOC_SCRATCH_BYTES ? fewest : w;
 }
 
@@ -304,12 +313,12 @@ static tv_status compress_check(const tv_dims *dims, const tv_cache *cache, cons
   return check_device();
 }
 
-// Argument checks of the verify call (no launch).
+// Argument checks of the verify call (no launch), and its workspace layout.
 static tv_status verify_check(const tv_dims *dims, const tv_cache *cache, const uint16_t *tree_u,
                               const uint64_t *anc, const int32_t *depth, const uint16_t *scr_c4,
                               const uint16_t *scr_c128, const uint16_t *q, const uint16_t *q_idx,
                               const uint16_t *w_idx, uint16_t *out, float *lse, int32_t *sel, int32_t *row_status,
-                              void *workspace, size_t workspace_bytes) {
+                              void *workspace, size_t workspace_bytes, WsLayout *layout) {
   tv_status st = check_dims(dims);
   if (st != TV_OK) return st;
   if (!cache_complete(*dims, cache) || !tree_u || !anc || !depth || !scr_c4 || !scr_c128 || !q || !q_idx || !w_idx ||
@@ -318,7 +327,7 @@ static tv_status verify_check(const tv_dims *dims, const tv_cache *cache, const 
   if (!cache_a16(cache) || !all_a16(tree_u, anc, depth, scr_c4, scr_c128, q, q_idx, w_idx, out, row_status) ||
       (lse && !a16(lse)) || (sel && !a16(sel)))
     return TV_ERR_INVALID_ARG;
-  const WsLayout w = ws_layout(*dims);
+  const WsLayout w = *layout = ws_layout(*dims);
   if (!workspace || workspace_bytes < w.total) return TV_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(workspace) & 255) return TV_ERR_INVALID_ARG;
   return check_device();
@@ -327,8 +336,7 @@ static tv_status verify_check(const tv_dims *dims, const tv_cache *cache, const 
 // The verify call's first kernel, the indexer scoring: it reads the committed
 // state and the indexer queries only, not the compression's scratch.
 static tv_status verify_score(const tv_dims &d, const tv_cache *cache, const uint16_t *q_idx, const uint16_t *w_idx,
-                              int32_t *row_status, void *workspace, hipStream_t stream) {
-  const WsLayout w = ws_layout(d);
+                              int32_t *row_status, void *workspace, const WsLayout &w, hipStream_t stream) {
   float *scores = reinterpret_cast<float *>(static_cast<char *>(workspace) + w.scores);
   TV_LAUNCH("indexer_score", launch_score(d, view(*cache), q_idx, w_idx, row_status, scores, w.score_stride, stream));
   return TV_OK;
@@ -340,9 +348,8 @@ static tv_status verify_score(const tv_dims &d, const tv_cache *cache, const uin
 static tv_status verify_rest(const tv_dims &d, const tv_cache *cache, const uint16_t *tree_u, const uint64_t *anc,
                              const int32_t *depth, const uint16_t *scr_c4, const uint16_t *scr_c128, const uint16_t *q,
                              const uint16_t *q_idx, const uint16_t *w_idx, uint16_t *out, float *lse, int32_t *sel,
-                             int32_t *row_status, void *workspace, hipStream_t stream,
+                             int32_t *row_status, void *workspace, const WsLayout &w, hipStream_t stream,
                              const uint16_t *hca_gate_w = nullptr, uint16_t *hca_out = nullptr) {
-  const WsLayout w = ws_layout(d);
   char *ws = static_cast<char *>(workspace);
   float *scores = reinterpret_cast<float *>(ws + w.scores);
   int32_t *selp = sel ? sel : reinterpret_cast<int32_t *>(ws + w.sel);
@@ -376,12 +383,13 @@ static tv_status verify_impl(const tv_dims *dims, const tv_cache *cache, const u
                               const uint16_t *scr_c128, const uint16_t *q, const uint16_t *q_idx,
                               const uint16_t *w_idx, uint16_t *out, float *lse, int32_t *sel, int32_t *row_status,
                               void *workspace, size_t workspace_bytes, hipStream_t stream) {
+  WsLayout w;
   tv_status st = verify_check(dims, cache, tree_u, anc, depth, scr_c4, scr_c128, q, q_idx, w_idx, out, lse, sel,
-                              row_status, workspace, workspace_bytes);
+                              row_status, workspace, workspace_bytes, &w);
   if (st != TV_OK) return st;
-  if ((st = verify_score(*dims, cache, q_idx, w_idx, row_status, workspace, stream)) != TV_OK) return st;
+  if ((st = verify_score(*dims, cache, q_idx, w_idx, row_status, workspace, w, stream)) != TV_OK) return st;
   return verify_rest(*dims, cache, tree_u, anc, depth, scr_c4, scr_c128, q, q_idx, w_idx, out, lse, sel, row_status,
-                     workspace, stream);
+                     workspace, w, stream);
 }
 
 // One layer's verify preprocess (with_mask), compression and verification.
@@ -395,12 +403,11 @@ static tv_status verify_impl(const tv_dims *dims, const tv_cache *cache, const u
 // compression.  Otherwise the calls' kernels in the calls' order.  Every part computes what it computes
 // in the separate calls, so the results are the same bits.  Arguments already
 // checked.
-static tv_status layer_step(const tv_dims *d, const tv_round &r, const tv_layer &L, bool with_mask,
+static tv_status layer_step(const tv_dims *d, const tv_round &r, const tv_layer &L, const WsLayout &w, bool with_mask,
                             hipStream_t stream) {
   const bool split = score_fast_path(*d) && compress_split(*d);
   const bool fused = (with_mask && score_fast_path(*d)) || split;
   if (fused) {
-    const WsLayout w = ws_layout(*d);
     float *scores = reinterpret_cast<float *>(static_cast<char *>(L.workspace) + w.scores);
     TV_LAUNCH("mask_score", launch_mask_score(*d, with_mask ? r.parents : nullptr, r.anc, r.depth, r.row_status,
                                               view(L.cache), L.q_idx,
@@ -416,11 +423,11 @@ static tv_status layer_step(const tv_dims *d, const tv_round &r, const tv_layer 
                                                  L.scr_c128, r.row_status, r.primary_last, L.cache.c4,
                                                  L.cache.c4_idx, stream));
   if (!fused) {
-    const tv_status st = verify_score(*d, &L.cache, L.q_idx, L.w_idx, r.row_status, L.workspace, stream);
+    const tv_status st = verify_score(*d, &L.cache, L.q_idx, L.w_idx, r.row_status, L.workspace, w, stream);
     if (st != TV_OK) return st;
   }
   return verify_rest(*d, &L.cache, L.tree_u, r.anc, r.depth, L.scr_c4, L.scr_c128, L.q, L.q_idx, L.w_idx, L.out,
-                     L.lse, L.sel, r.row_status, L.workspace, stream, split ? L.gate_w : nullptr,
+                     L.lse, L.sel, r.row_status, L.workspace, w, stream, split ? L.gate_w : nullptr,
                      split ? L.scr_c128 : nullptr);
 }
 
@@ -440,12 +447,13 @@ static tv_status commit_check(const tv_dims *dims, const tv_cache *cache, const 
   return check_device();
 }
 
-static tv_status layer_check(const tv_dims *d, const tv_round &r, const tv_layer &L) {
+// Argument checks of a layer's step (no launch), and its workspace layout.
+static tv_status layer_check(const tv_dims *d, const tv_round &r, const tv_layer &L, WsLayout *layout) {
   tv_status st = compress_check(d, &L.cache, L.tree_u, r.anc, r.depth, L.gate_w, L.scr_c4, L.scr_c128, r.row_status,
                                 r.primary_last);
   if (st != TV_OK) return st;
   return verify_check(d, &L.cache, L.tree_u, r.anc, r.depth, L.scr_c4, L.scr_c128, L.q, L.q_idx, L.w_idx, L.out,
-                      L.lse, L.sel, r.row_status, L.workspace, L.workspace_bytes);
+                      L.lse, L.sel, r.row_status, L.workspace, L.workspace_bytes, layout);
 }
 
 }  // namespace tv
@@ -486,11 +494,12 @@ tv_status tv_branch_compress(const tv_dims *dims, const tv_cache *cache, const u
 tv_status tv_verify_round(const tv_dims *dims, const tv_round *round, const tv_layer *layer, hipStream_t stream) {
   if (!round || !layer) return TV_ERR_INVALID_ARG;
   const bool with_mask = round->parents != nullptr;  // NULL: anc and depth already hold this round's mask
-  tv_status st = layer_check(dims, *round, *layer);
+  WsLayout w;
+  tv_status st = layer_check(dims, *round, *layer, &w);
   if (st != TV_OK) return st;
   if (with_mask && (st = mask_check(dims, round->parents, round->anc, round->depth, round->row_status)) != TV_OK)
     return st;
-  return layer_step(dims, *round, *layer, with_mask, stream);
+  return layer_step(dims, *round, *layer, w, with_mask, stream);
 }
 
 size_t tv_verify_workspace_bytes(const tv_dims *dims) {
@@ -579,7 +588,8 @@ namespace tv {
 static tv_status record_round(const tv_dims *d, const tv_round &r, const tv_layer *layers, int n, hipStream_t s) {
   tv_status st = mask_check(d, r.parents, r.anc, r.depth, r.row_status);
   for (int l = 0; l < n && st == TV_OK; ++l) {  // each layer as tv_verify_round runs it, the mask with layer 0
-    if ((st = layer_check(d, r, layers[l])) == TV_OK) st = layer_step(d, r, layers[l], l == 0, s);
+    WsLayout w;
+    if ((st = layer_check(d, r, layers[l], &w)) == TV_OK) st = layer_step(d, r, layers[l], w, l == 0, s);
   }
   if (st == TV_OK && r.target_logits)
     st = tv_select_accepted_path(d, r.parents, r.anc, r.depth, r.draft_tokens, r.target_logits, r.vocab,
