@@ -127,7 +127,8 @@ static int32_t least_splits(int64_t mk) { return (int32_t)((mk + kAttnMaxChunk -
 // h1: 61.5; 192 nodes, 32 a row, 1: 57.6, 2: 83.8, h1: 68.3.  8 heads: 8 nodes of
 // 776 keys 1: 38.1, 3: 30.2, 8: 26.7; 222 nodes of 404 keys 1: 39.4, 2: 40.9.
 // Every call makes its plan anew, so the search steps over the chunk sizes that
-// differ, not over all split counts.
+// differ, not over all split counts: from one split count to the smallest that
+// gives a smaller chunk, which is always larger than it.
 SplitPlan split_plan(const tv_dims &d) {
   const SplitCost k = split_cost(d);
   const int64_t mk = max_keys_of(d);
@@ -140,7 +141,7 @@ SplitPlan split_plan(const tv_dims &d) {
   SplitPlan best{};
   float best_cost = INFINITY;
   for (int halves = 1; halves <= (d.H == 64 ? 2 : 1); ++halves)
-    for (int32_t s = least; s <= tiles;) {
+    for (int32_t s = least;;) {
       const int32_t ct = (tiles + s - 1) / s;
       const SplitPlan p = plan_of(mk, tiles, ct, halves);
       const int64_t wgs = per_xcd(p.splits, halves);
@@ -152,7 +153,8 @@ SplitPlan split_plan(const tv_dims &d) {
         best = p;
         best_cost = c;
       }
-      s = p.splits + 1;
+      if (ct == 1) break;
+      s = (tiles + ct - 2) / (ct - 1);
     }
   return best;
 }
