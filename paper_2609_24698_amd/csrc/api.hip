@@ -191,8 +191,8 @@ static WsLayout ws_layout_of(const tv_dims &d, const SplitPlan &plan) {
   off = align256(off + sizeof(int32_t) * surv);
   w.surv_key = off;
   off = align256(off + sizeof(uint32_t) * surv);
-  w.surv_cnt = off;
-  off = align256(off + 2 * sizeof(int32_t) * (tseg > 1 ? nodes * tseg : 0));
+  w.surv_worst = off;
+  off = align256(off + sizeof(uint32_t) * (tseg > 1 ? nodes * tseg : 0));
   w.total = off;
   return w;
 }
@@ -365,14 +365,14 @@ static tv_status verify_rest(const tv_dims &d, const tv_cache *cache, const uint
   int32_t *nkeys_rank = reinterpret_cast<int32_t *>(ws + w.nkeys_rank);
   int32_t *surv_idx = reinterpret_cast<int32_t *>(ws + w.surv_idx);
   uint32_t *surv_key = reinterpret_cast<uint32_t *>(ws + w.surv_key);
-  int32_t *surv_cnt = reinterpret_cast<int32_t *>(ws + w.surv_cnt);
+  uint32_t *surv_worst = reinterpret_cast<uint32_t *>(ws + w.surv_worst);
   TV_LAUNCH("topk_select", launch_topk(d, cv, tree_u, anc, depth, scr_c4, scr_c128, q_idx, w_idx, scores,
                                        w.score_stride, selp, row_status, row_order, row_rank, keytab, w.plan.max_keys,
-                                       nkeys, nkeys_rank, surv_idx, surv_key, surv_cnt, hca_gate_w, hca_out,
+                                       nkeys, nkeys_rank, surv_idx, surv_key, surv_worst, hca_gate_w, hca_out,
                                        stream));
   if (topk_max_segments(d) > 1)
     TV_LAUNCH("topk_merge", launch_topk_merge(d, cv, anc, depth, scr_c4, selp, row_status, row_rank, keytab,
-                                              w.plan.max_keys, surv_idx, surv_key, surv_cnt, stream));
+                                              w.plan.max_keys, surv_idx, surv_key, surv_worst, stream));
   TV_LAUNCH("verify_attn", launch_attn(d, q, row_status, row_order, keytab, nkeys_rank, w.plan, part_o, part_ml, out,
                                        lse, stream));
   if (w.plan.splits > 1)

@@ -63,6 +63,7 @@ constexpr uint32_t kPadKey = 0xFFFFFFFFu;
 constexpr int kMergeWideBits = 26;  // a merge whose distances have more bits takes the wide first digit
 static_assert(kTkNT * kTkKPT == kTopkSeg, "a segment fills whole slots");
 static_assert(kMaxScratch <= 64, "the path entries fit the first wavefront's path slot");
+static_assert(kTkMaxK < kTopkSeg, "a full segment has more candidates than a node keeps");
 
 // Histogram words of the three passes: 13, 11 and 8 bits (a digit of up to 11 bits spreads over 2048 words), or
 // 11, 11 and 10 bits in the same words.
@@ -416,7 +417,7 @@ __device__ __forceinline__ void topk_node(const tv_dims &d, const CacheView &c, 
                                           const uint16_t **__restrict__ keytab, int keytab_stride,
                                           int32_t *__restrict__ nkeys_tab, int32_t *__restrict__ nkeys_rank,
                                           int max_seg, int32_t *__restrict__ surv_idx,
-                                          uint32_t *__restrict__ surv_key, int32_t *__restrict__ surv_cnt, int blk,
+                                          uint32_t *__restrict__ surv_key, uint32_t *__restrict__ surv_worst, int blk,
                                           TopkSmem &sm) {
   SelShared<kTkNT> &sh = sm.sh;
   float *scr_score = sm.scr_score;
@@ -612,9 +613,8 @@ __device__ __forceinline__ void topk_node(const tv_dims &d, const CacheView &c, 
       surv_idx[sv + t] = e < 0 ? -1 : (e < cn ? c0 + e : n4 + (e - cn));
       surv_key[sv + t] = e < 0 ? kPadKey : live_key(e < cn ? sc[e] : scr_score[e - cn]);
     }
-    // survivors, and a key none of the segment's k best exceeds (none when it has fewer)
-    if (tid == 0)
-      reinterpret_cast<int2 *>(surv_cnt)[node * max_seg + seg] = make_int2(all ? seg_n : k, (int)(all ? kPadKey - 1u : worst));
+    // a key none of the segment's k best exceeds (no bound when it has fewer)
+    if (tid == 0) surv_worst[node * max_seg + seg] = all ? kPadKey - 1u : worst;
   }
 }
 
@@ -625,10 +625,10 @@ __global__ void __launch_bounds__(kTkNT) __attribute__((amdgpu_waves_per_eu(4)))
     int score_stride, int32_t *__restrict__ sel, int32_t *__restrict__ row_status, int32_t *__restrict__ row_order,
     int32_t *__restrict__ row_rank, const uint16_t **__restrict__ keytab, int keytab_stride,
     int32_t *__restrict__ nkeys_tab, int32_t *__restrict__ nkeys_rank, int max_seg, int32_t *__restrict__ surv_idx,
-    uint32_t *__restrict__ surv_key, int32_t *__restrict__ surv_cnt) {
+    uint32_t *__restrict__ surv_key, uint32_t *__restrict__ surv_worst) {
   __shared__ TopkSmem sm;
   topk_node(d, c, tree_u, anc, depth, scr_c4, scr_c128, q_idx, w_idx, scores, score_stride, sel, row_status,
-            row_order, row_rank, keytab, keytab_stride, nkeys_tab, nkeys_rank, max_seg, surv_idx, surv_key, surv_cnt,
+            row_order, row_rank, keytab, keytab_stride, nkeys_tab, nkeys_rank, max_seg, surv_idx, surv_key, surv_worst,
             blockIdx.x, sm);
 }
 
@@ -644,7 +644,7 @@ __global__ void __launch_bounds__(kTkNT) __attribute__((amdgpu_waves_per_eu(4)))
     int score_stride, int32_t *__restrict__ sel, int32_t *__restrict__ row_status, int32_t *__restrict__ row_order,
     int32_t *__restrict__ row_rank, const uint16_t **__restrict__ keytab, int keytab_stride,
     int32_t *__restrict__ nkeys_tab, int32_t *__restrict__ nkeys_rank, int max_seg, int32_t *__restrict__ surv_idx,
-    uint32_t *__restrict__ surv_key, int32_t *__restrict__ surv_cnt, const uint16_t *__restrict__ gate_w) {
+    uint32_t *__restrict__ surv_key, uint32_t *__restrict__ surv_worst, const uint16_t *__restrict__ gate_w) {
   static_assert(kTkNT == kHcaNT, "one workgroup size for both roles");
   __shared__ union {
     TopkSmem t;
@@ -654,14 +654,16 @@ __global__ void __launch_bounds__(kTkNT) __attribute__((amdgpu_waves_per_eu(4)))
   if ((int)blockIdx.x < ntk)
     topk_node(d, c, tree_u, anc, depth, scr_c4, scr_c128, q_idx, w_idx, scores, score_stride, sel, row_status,
               row_order, row_rank, keytab, keytab_stride, nkeys_tab, nkeys_rank, max_seg, surv_idx, surv_key,
-              surv_cnt, blockIdx.x, sm.t);
+              surv_worst, blockIdx.x, sm.t);
   else
     hca_node(d, c, tree_u, anc, depth, gate_w, scr_c128, row_status, false, blockIdx.x - ntk, sm.h);
 }
 
 // Merge of a segmented node: the topk of the survivors of all its segments.
 // Segment s holds k slots (survivors in index order, then padding kPadKey), so
-// the slots of all segments in order list the survivors in index order.
+// the slots of all segments in order list the survivors in index order.  Every
+// segment but the last is full and fills its k slots, and the last has a
+// candidate, so there are always more than k survivors.
 template <int NT>
 __global__ void __launch_bounds__(NT, 1) topk_merge_kernel(tv_dims d, CacheView c, const uint64_t *__restrict__ anc,
                                                            const int32_t *__restrict__ depth,
@@ -672,9 +674,8 @@ __global__ void __launch_bounds__(NT, 1) topk_merge_kernel(tv_dims d, CacheView 
                                                            const uint16_t **__restrict__ keytab, int keytab_stride,
                                                            int max_seg, const int32_t *__restrict__ surv_idx,
                                                            const uint32_t *__restrict__ surv_key,
-                                                           const int32_t *__restrict__ surv_cnt) {
+                                                           const uint32_t *__restrict__ surv_worst) {
   __shared__ SelShared<NT> sh;
-  __shared__ int real_cnt;
   __shared__ uint32_t worst_key;
   __shared__ int32_t path[64], hca_node[64];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -693,8 +694,7 @@ __global__ void __launch_bounds__(NT, 1) topk_merge_kernel(tv_dims d, CacheView 
   const uint64_t m = anc[node];
   const int dl = lane < d.D ? depth[(int64_t)b * d.D + lane] : 0;
   const int64_t sv = (int64_t)node * max_seg * k;
-  const int2 seg_s =  // max_seg <= 64: wave 0
-      tid < max_seg ? reinterpret_cast<const int2 *>(surv_cnt)[node * max_seg + tid] : make_int2(0, 0);
+  const uint32_t seg_worst = tid < max_seg ? surv_worst[node * max_seg + tid] : kPadKey - 1u;  // max_seg <= 64: wave 0
   const int all_slots = max_seg * k;
   constexpr int KPT = kTopkMergeCap / NT;
   static_assert(KPT * NT == kTopkMergeCap, "merge capacity");
@@ -719,21 +719,15 @@ __global__ void __launch_bounds__(NT, 1) topk_merge_kernel(tv_dims d, CacheView 
   best = ~wave_max_u32(~best);
   if (lane == 0) sh.wsum[tid >> 6] = best;
   if (tid < 64) {
-    const int run = (int)wave_total(tid < nseg ? (uint32_t)seg_s.x : 0u);
-    const uint32_t w = ~wave_max_u32(~(tid < nseg && seg_s.x == k ? (uint32_t)seg_s.y : kPadKey - 1u));
-    if (tid == 0) {
-      real_cnt = run;
-      worst_key = w;
-    }
+    const uint32_t w = ~wave_max_u32(~(tid < nseg ? seg_worst : kPadKey - 1u));
+    if (tid == 0) worst_key = w;
   }
   uint64_t csa_mask;
   const NodeKeys nk = path_keys(d, L, i, m, dl, path, hca_node, csa_mask);
-  __syncthreads();  // the survivors' totals and bounds, the clear histograms and the node's path are visible
-  const int total = real_cnt;
+  __syncthreads();  // the survivors' bounds, the clear histograms and the node's path are visible
   const uint16_t **tab = keytab + ((int64_t)rank * d.D + i) * keytab_stride;  // kept by (rank, node)
   int32_t *out = sel + node * k;
   const int nr = (slots + NT - 1) / NT;
-  const bool all = total <= k;  // every real survivor is taken
   // The survivors' keys crowd into a few exponents, where a digit of leading
   // bits would put thousands of them on one counter.  The digits are therefore
   // taken from the distance to the best key, and a survivor beyond the worst
@@ -745,24 +739,21 @@ __global__ void __launch_bounds__(NT, 1) topk_merge_kernel(tv_dims d, CacheView 
   const uint32_t pad = bits == 32 ? kPadKey : (1u << bits) - 1u;  // above every distance
 #pragma unroll
   for (int j = 0; j < KPT; ++j) key[j] = key[j] <= worst ? key[j] - best : pad;
-  Threshold t{pad - 1u, kPadKey, 0, true};
+  Threshold t;
   // Survivors of both signs span most of the 32 bits (few keys lie far from
   // zero): 11 bits of that put thousands on one counter (6,324 of 30,828 on a
   // 1M-token node, the merge 27 us), so such nodes take the wide first digit.
-  if (!all) {
-    if (bits > kMergeWideBits)
-      t = radix_threshold<true, KPT>(key, nr, pad, false, k, bits, sh);
-    else
-      t = radix_threshold<false, KPT>(key, nr, pad, false, k, bits, sh);
-  }
+  if (bits > kMergeWideBits)
+    t = radix_threshold<true, KPT>(key, nr, pad, false, k, bits, sh);
+  else
+    t = radix_threshold<false, KPT>(key, nr, pad, false, k, bits, sh);
   if (t.all_eq)
     compact_words<true, KPT>(key, nr, pad, false, 0, t, pad, sh);
   else
     compact_words<false, KPT>(key, nr, pad, false, 0, t, pad, sh);
   lds_barrier();  // the list is complete
-  const int taken = all ? total : k;
   for (int t = tid; t < k; t += NT) {
-    const int s = t < taken ? surv_idx[sv + std::min(std::max(sh.list[t], 0), slots - 1)] : -1;
+    const int s = surv_idx[sv + std::min(std::max(sh.list[t], 0), slots - 1)];
     out[t] = s;
     if (s >= 0) tab[t] = csa_row(d, nk, b, s, path, c.c4, c4b, c.page_table, scr_c4);
   }
@@ -783,7 +774,7 @@ hipError_t launch_topk(const tv_dims &d, const CacheView &c, const uint16_t *tre
                        const uint16_t *w_idx, const float *scores, int32_t score_stride, int32_t *sel,
                        int32_t *row_status, int32_t *row_order, int32_t *row_rank, const uint16_t **keytab,
                        int32_t keytab_stride, int32_t *nkeys, int32_t *nkeys_rank, int32_t *surv_idx,
-                       uint32_t *surv_key, int32_t *surv_cnt, const uint16_t *hca_gate_w, uint16_t *hca_out,
+                       uint32_t *surv_key, uint32_t *surv_worst, const uint16_t *hca_gate_w, uint16_t *hca_out,
                        hipStream_t s) {
   if (d.D > kMaxScratch || !topk_supported(d)) return hipErrorInvalidValue;
   const int max_seg = topk_max_segments(d);
@@ -795,26 +786,26 @@ hipError_t launch_topk(const tv_dims &d, const CacheView &c, const uint16_t *tre
     topk_hca_kernel<<<(unsigned)(ntk + (int64_t)d.B * d.D), kTkNT, 0, s>>>(
         d, c, tree_u, anc, depth, scr_c4, hca_out, q_idx, w_idx, scores, score_stride, sel,
         row_status, row_order, row_rank, keytab, keytab_stride, nkeys, nkeys_rank, max_seg, surv_idx, surv_key,
-        surv_cnt, hca_gate_w);
+        surv_worst, hca_gate_w);
     return hipGetLastError();
   }
   topk_kernel<<<(unsigned)ntk, kTkNT, 0, s>>>(
       d, c, tree_u, anc, depth, scr_c4, scr_c128, q_idx, w_idx, scores, score_stride, sel, row_status, row_order,
-      row_rank, keytab, keytab_stride, nkeys, nkeys_rank, max_seg, surv_idx, surv_key, surv_cnt);
+      row_rank, keytab, keytab_stride, nkeys, nkeys_rank, max_seg, surv_idx, surv_key, surv_worst);
   return hipGetLastError();
 }
 
 hipError_t launch_topk_merge(const tv_dims &d, const CacheView &c, const uint64_t *anc, const int32_t *depth,
                              const uint16_t *scr_c4, int32_t *sel, const int32_t *row_status,
                              const int32_t *row_rank, const uint16_t **keytab, int32_t keytab_stride,
-                             const int32_t *surv_idx, const uint32_t *surv_key, const int32_t *surv_cnt,
+                             const int32_t *surv_idx, const uint32_t *surv_key, const uint32_t *surv_worst,
                              hipStream_t s) {
   const int max_seg = topk_max_segments(d);
   if (max_seg <= 1) return hipSuccess;
   topk_merge_kernel<kMergeNT><<<(unsigned)((int64_t)d.B * d.D), kMergeNT, 0, s>>>(d, c, anc, depth, scr_c4, sel,
                                                                                  row_status,
                                                                      row_rank, keytab, keytab_stride, max_seg,
-                                                                     surv_idx, surv_key, surv_cnt);
+                                                                     surv_idx, surv_key, surv_worst);
   return hipGetLastError();
 }
 

@@ -52,7 +52,7 @@ struct WsLayout {
   size_t nkeys_rank;  // int32 [B rank][D]: the same counts by rank (0 for a skipped row)
   size_t surv_idx;    // int32 [B*D][topk segments][topk]: survivors of each top-k segment (segmented nodes only)
   size_t surv_key;    // uint32, same shape: their score keys
-  size_t surv_cnt;    // int32 [B*D][topk segments][2]: survivors, and a score key none of them exceeds
+  size_t surv_worst;  // uint32 [B*D][topk segments]: a score key none of the segment's topk best exceeds
   size_t total;
   int32_t score_stride;
   SplitPlan plan;
@@ -111,12 +111,12 @@ hipError_t launch_topk(const tv_dims &d, const CacheView &c, const uint16_t *tre
                        const uint16_t *w_idx, const float *scores, int32_t score_stride, int32_t *sel,
                        int32_t *row_status, int32_t *row_order, int32_t *row_rank, const uint16_t **keytab,
                        int32_t keytab_stride, int32_t *nkeys, int32_t *nkeys_rank, int32_t *surv_idx,
-                       uint32_t *surv_key, int32_t *surv_cnt, const uint16_t *hca_gate_w, uint16_t *hca_out,
+                       uint32_t *surv_key, uint32_t *surv_worst, const uint16_t *hca_gate_w, uint16_t *hca_out,
                        hipStream_t s);
 hipError_t launch_topk_merge(const tv_dims &d, const CacheView &c, const uint64_t *anc, const int32_t *depth,
                              const uint16_t *scr_c4, int32_t *sel, const int32_t *row_status,
                              const int32_t *row_rank, const uint16_t **keytab, int32_t keytab_stride,
-                             const int32_t *surv_idx, const uint32_t *surv_key, const int32_t *surv_cnt,
+                             const int32_t *surv_idx, const uint32_t *surv_key, const uint32_t *surv_worst,
                              hipStream_t s);
 hipError_t launch_attn(const tv_dims &d, const uint16_t *q, const int32_t *row_status, const int32_t *row_order,
                        const uint16_t *const *keytab, const int32_t *nkeys, const SplitPlan &plan, float *part_o,

@@ -38,7 +38,7 @@ def _total(d, splits):
         parts += [4 * nodes * splits * d["H"] * d["d_v"], 8 * nodes * splits * d["H"]]
     parts += [4 * d["B"]] * 2 + [8 * nodes * mk] + [4 * nodes] * 2
     if seg > 1:
-        parts += [4 * nodes * seg * d["topk"]] * 2 + [8 * nodes * seg]
+        parts += [4 * nodes * seg * d["topk"]] * 2 + [4 * nodes * seg]
     return sum((p + 255) // 256 * 256 for p in parts)
 
 
@@ -132,3 +132,18 @@ def test_plan_is_the_cheapest():
         assert got == want, (d, splits)
         seen.add(splits)
     assert len(seen) > 20
+
+
+def test_noalloc_limit_to_the_byte():
+    """Dims whose workspace ends within a few bytes per top-k segment of that
+    entry's array: one word a segment beside its survivors is all that fits."""
+    limit, rng, dims = binding.NOALLOC_SCRATCH_BYTES, random.Random(23), []
+    while len(dims) < 12:
+        B, D, topk = rng.randint(8, 40), rng.randint(1, 16), rng.choice([300, 512, 777, 2048])
+        max_len = rng.randint(4 * (SEG + 1), 1 << 20)
+        d = _dims(rng.choice((64, 8)), B, D, topk, max_len)
+        seg = -(-(max_len // 4) // SEG)
+        if seg * topk <= 34816 and limit - 4 * B * D * seg < _least_total(d) <= limit:
+            dims.append(d)
+    for d, got in zip(dims, _sizes_of(dims)):
+        assert 0 < got <= limit, (d, got)
