@@ -12,7 +12,8 @@
 // list of all valid rows, so ragged lengths cost no idle workgroups.  Fast
 // path (H_idx = 8): one 4-wavefront workgroup per (row, 256-entry chunk), the
 // chunk body shared with the mask-and-scoring kernel; a tree of more than
-// eight nodes is scored in groups of eight (score_kernel_h8_groups).
+// eight nodes is scored in groups of eight by a persistent grid over the live
+// chunks (score_kernel_h8_groups).
 #include <algorithm>
 
 #include "score_h8.h"
@@ -168,28 +169,84 @@ __global__ void __launch_bounds__(256) score_kernel_h8(tv_dims d, CacheView c, c
 
 // Trees of more than eight nodes, H_idx = 8: the fast path's chunk for each
 // group of eight nodes.  What bounds it: with few chunks the chain of one
-// (two round trips, a tile's products), so every (chunk, group) is then a
-// workgroup of its own and the keys are read again per group; with
-// kGroupGrid chunks or more the chip is full without that, and one workgroup
-// takes all groups of its chunk from keys held in registers.  The general path
+// (two round trips, a tile's products), so every (chunk, group) is then a unit
+// of its own and the keys are read again per group; with kGroupChunks chunks or
+// more the chip is full without that, and a unit is a chunk with all of its
+// groups, from keys held in registers.  The general path
 // spends its time instead in a head reduction through LDS, a barrier pair per
 // group and queries read per lane from memory: six rows of 32 nodes with up to
-// 6,000 entries took 35.7 us in it and take 7.3 here.
-constexpr int kGroupGrid = 1024;
+// 6,000 entries took 35.7 us in it and take 7.4 here; 64 rows of 12 nodes with
+// up to 4,096 entries 20.2 and 8.1.
+//
+// The units are those of the rows' lengths, counted by every workgroup, and the
+// workgroups that are resident together stride over them: max_len, which only
+// bounds the lengths, neither adds workgroups nor decides the split.  32 rows
+// of 9 nodes with up to 500 entries and a max_len of 1M take 6.4 us (15.7 in the
+// general path, 42.0 with a workgroup for every chunk of max_len); 300 such rows
+// with a max_len of 64K 12.0 (22.4, 87.6).
+constexpr int kGroupChunks = 1024;
+constexpr int kGroupGrid = 768;  // three workgroups a compute unit (registers)
 template <bool FP8>
-__global__ void __launch_bounds__(256) score_kernel_h8_groups(tv_dims d, CacheView c,
+__global__ void __launch_bounds__(256, 3) score_kernel_h8_groups(tv_dims d, CacheView c,
                                                               const uint16_t *__restrict__ q_idx,
                                                               const uint16_t *__restrict__ w_idx,
                                                               const int32_t *__restrict__ row_status,
-                                                              float *__restrict__ scores, int score_stride,
-                                                              int chunks_per_row, int groups, int groups_per_wg) {
+                                                              float *__restrict__ scores, int score_stride) {
   __shared__ ScoreH8Smem<4> sm;
-  const int parts = (groups + groups_per_wg - 1) / groups_per_wg;
-  const int k = blockIdx.x / parts;
-  const int g0 = (blockIdx.x - k * parts) * groups_per_wg;
-  const int b = k / chunks_per_row;
-  score_h8_chunk<FP8, 4, true, true>(d, c, q_idx, w_idx, row_status, scores, score_stride, b, k - b * chunks_per_row,
-                                     sm, g0, std::min(groups, g0 + groups_per_wg));
+  __shared__ uint32_t blk_sum[kMaxB / 64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int blocks = (d.B + 63) / 64;  // of 64 rows, one per lane
+  struct Row {
+    int32_t L;
+    int64_t c4;
+    uint32_t chunks, before;  // the row's, and those of the block's rows before it
+  };
+  auto rows_of = [&](int blk) {
+    const int b = std::min(64 * blk + lane, d.B - 1);
+    Row r;
+    r.L = c.len[b];
+    r.c4 = d.page_size == 0 ? c.c4_base[b] : 0;
+    const bool ok = row_status[b] == TV_ROW_OK && len_ok(r.L, d.max_len) && 64 * blk + lane < d.B;
+    r.chunks = ok ? (uint32_t)(r.L / d.ratio_csa + 255) / 256u : 0u;
+    r.before = wave_prefix_sum(r.chunks) - r.chunks;
+    return r;
+  };
+  Row row = rows_of(0);
+  uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)(row.before + row.chunks), 63);
+  uint32_t blk_chunks = 0u, blk_before = 0u;  // lane j: of block j, and of the blocks before it
+  if (blocks > 1) {
+    for (int j = wv; j < blocks; j += 4) {
+      const Row r = rows_of(j);
+      if (lane == 63) blk_sum[j] = r.before + r.chunks;
+    }
+    __syncthreads();
+    blk_chunks = lane < blocks ? blk_sum[lane] : 0u;
+    const uint32_t incl = wave_prefix_sum(blk_chunks);
+    blk_before = incl - blk_chunks;
+    total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+  }
+  const uint32_t groups = (uint32_t)(d.D + 7) / 8u;
+  const uint32_t per_unit = total >= kGroupChunks ? groups : 1u, parts = groups / per_unit;
+  for (uint32_t u = blockIdx.x; u < total * parts; u += gridDim.x) {
+    uint32_t k = u / parts;
+    const int g0 = (int)((u - k * parts) * per_unit);
+    int blk = 0;
+    if (blocks > 1) {
+      const uint64_t in = __builtin_amdgcn_ballot_w64(k >= blk_before && k - blk_before < blk_chunks);
+      blk = __ffsll((unsigned long long)in) - 1;
+      k -= (uint32_t)__builtin_amdgcn_readlane((int)blk_before, blk);
+      row = rows_of(blk);
+    }
+    const uint64_t in = __builtin_amdgcn_ballot_w64(k >= row.before && k - row.before < row.chunks);
+    const int f = __ffsll((unsigned long long)in) - 1;
+    const int ch = (int)(k - (uint32_t)__builtin_amdgcn_readlane((int)row.before, f));
+    const int64_t c4 = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(row.c4 >> 32), f) << 32) |
+                                 (uint32_t)__builtin_amdgcn_readlane((int)row.c4, f));
+    score_h8_chunk<FP8, 4, false, true>(d, c, q_idx, w_idx, nullptr, scores, score_stride, 64 * blk + f, ch, sm, g0,
+                                        g0 + (int)per_unit, __builtin_amdgcn_readlane(row.L, f), c4);
+    __syncthreads();  // the chunk's queries and weights are read out
+  }
 }
 
 bool score_fast_path(const tv_dims &d) { return d.H_idx == 8 && d.D <= 8; }
@@ -207,17 +264,12 @@ hipError_t launch_score(const tv_dims &d, const CacheView &c, const uint16_t *q_
     return hipGetLastError();
   }
   if (d.H_idx == 8) {
-    const int chunks = std::max(1, (d.max_len / d.ratio_csa + 255) / 256);
-    const int groups = (d.D + 7) / 8;
-    const int per_wg = (int64_t)d.B * chunks >= kGroupGrid ? groups : 1;
-    const int64_t grid = (int64_t)d.B * chunks * (groups / per_wg);
-    if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
+    const int64_t chunks = std::max(1, (d.max_len / d.ratio_csa + 255) / 256);
+    const int grid = (int)std::min<int64_t>(d.B * chunks * ((d.D + 7) / 8), kGroupGrid);
     if (d.idx_fmt == TV_IDX_E4M3)
-      score_kernel_h8_groups<true><<<(unsigned)grid, 256, 0, s>>>(d, c, q_idx, w_idx, row_status, scores, score_stride,
-                                                                 chunks, groups, per_wg);
+      score_kernel_h8_groups<true><<<grid, 256, 0, s>>>(d, c, q_idx, w_idx, row_status, scores, score_stride);
     else
-      score_kernel_h8_groups<false><<<(unsigned)grid, 256, 0, s>>>(d, c, q_idx, w_idx, row_status, scores, score_stride,
-                                                                  chunks, groups, per_wg);
+      score_kernel_h8_groups<false><<<grid, 256, 0, s>>>(d, c, q_idx, w_idx, row_status, scores, score_stride);
     return hipGetLastError();
   }
   const int64_t upper = (int64_t)d.B * ((d.max_len / d.ratio_csa + kScoreChunk - 1) / kScoreChunk);

@@ -53,7 +53,9 @@ struct ScoreH8Smem {
 // is one group (D <= 8).  The
 // loads a chunk needs (row status, length, pool base, indexer weights, then
 // queries and keys) are issued as early as their addresses are known, so a
-// chunk costs two memory round trips.  kStatus: a row whose status is not
+// chunk costs two memory round trips; a kMulti caller, which had to look at
+// every row's length to find the chunk, passes the row's length and pool base
+// (row_len, row_c4) and a row that is to be scored.  kStatus: a row whose status is not
 // TV_ROW_OK is skipped (only where nothing writes the status meanwhile, so the
 // exit is workgroup-uniform; the length exits always are).
 template <bool FP8, int NW, bool kStatus, bool kMulti = false>
@@ -62,26 +64,26 @@ __device__ __forceinline__ void score_h8_chunk(const tv_dims &d, const CacheView
                                                const uint16_t *__restrict__ w_idx,
                                                const int32_t *__restrict__ row_status, float *__restrict__ scores,
                                                int score_stride, int b, int ch, ScoreH8Smem<NW> &sm, int g0 = 0,
-                                               int g1 = 1) {
+                                               int g1 = 1, int32_t row_len = 0, int64_t row_c4 = 0) {
   constexpr int kChunk = NW * 64;
   constexpr int kQU = (512 + 64 * NW - 1) / (64 * NW);  // 16-byte query pieces per thread (64 rows x 8)
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int l32 = lane & 31, hi = lane >> 5;
   const int M = d.D * 8;
   const int32_t status = kStatus ? row_status[b] : TV_ROW_OK;
-  const int32_t L = c.len[b];
+  const int32_t L = kMulti ? row_len : c.len[b];
   const bool flat = d.page_size == 0;
-  const int64_t c4b = flat ? c.c4_base[b] : 0;
+  const int64_t c4b = kMulti ? row_c4 : flat ? c.c4_base[b] : 0;
   // Row r of group g is query row 64 g + r of the tree; rows past M are zero.
   auto weight = [&](int g) {
     const int r = 64 * g + tid;
     return tid < 64 && r < M ? bf2f(w_idx[(int64_t)b * M + r]) : 0.f;
   };
   float wv_ = weight(kMulti ? g0 : 0);
-  if (status != TV_ROW_OK || !len_ok(L, d.max_len)) return;
+  if (!kMulti && (status != TV_ROW_OK || !len_ok(L, d.max_len))) return;
   const int n4 = L / d.ratio_csa;
   const int e0 = ch * kChunk + wv * 64;
-  if (ch * kChunk >= n4) return;
+  if (!kMulti && ch * kChunk >= n4) return;
   // Operands are read as whole 128-byte rows (eight lanes a row, eight rows a
   // load) and turned into the MFMA layout through LDS: lane l32 + 32 hi holds
   // channels 16 ks + 8 hi of its row.  In a tile, 16-byte slot c of row r sits
