@@ -114,10 +114,19 @@ static int64_t max_keys_of(const tv_dims &d) {
 // The fewest splits, by the pointer table's bound.
 static int32_t least_splits(int64_t mk) { return (int32_t)((mk + kAttnMaxChunk - 1) / kAttnMaxChunk); }
 
+// A plan is made from bounds, and rows may hold far fewer keys than max_keys: a
+// row of 100 tokens pays for the combine (2.5 to 3 us) and saves nothing.  So
+// nodes of fewer keys than kSplitKeys, whose tiles are soon done, and batches
+// of kSplitNodes nodes or more, which fill the chip by themselves, keep the
+// fewest splits.  8 heads, steps in us, one split and the cheapest count: 32
+// nodes of up to 459 keys, rows full 29.7 and 24.9, of 100 tokens 21.5 and 24.7;
+// 256 nodes of up to 712 keys, full 38.8 and 38.2, of 1,024 tokens 29.5 and 35.3.
+constexpr int kSplitKeys = 512, kSplitNodes = 256;
+
 // The cheapest plan by the cost above: a workgroup or two (half the heads each,
 // no partials to merge) per split, and the fewest splits the pointer table
 // allows or as many as still run at once (one more round of workgroups costs
-// more than any plan saves).  An XCD gets whole rows when there are 8 or more
+// more than any plan saves), if the sizes are worth a split at all.  An XCD gets whole rows when there are 8 or more
 // (unit_of), so the fullest XCD decides: 12 rows of 7 nodes fill 14 of its 32
 // compute units whole and need two rounds in three splits.  Measured, 64 heads,
 // about 712 keys, steps in us by splits (h: in halves): 8 nodes 1: 41.0, 4: 34.7,
@@ -138,6 +147,7 @@ SplitPlan split_plan(const tv_dims &d) {
     if (d.B >= 8) return (int64_t)((d.B + 7) / 8) * d.D * halves * splits;
     return (nodes * halves * attn_padded_splits(d.B, splits) + 7) / 8;
   };
+  const bool split = mk >= kSplitKeys && nodes < kSplitNodes;
   SplitPlan best{};
   float best_cost = INFINITY;
   for (int halves = 1; halves <= (d.H == 64 ? 2 : 1); ++halves)
@@ -153,7 +163,7 @@ SplitPlan split_plan(const tv_dims &d) {
         best = p;
         best_cost = c;
       }
-      if (ct == 1) break;
+      if (!split || ct == 1) break;
       s = (tiles + ct - 2) / (ct - 1);
     }
   return best;

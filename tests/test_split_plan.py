@@ -88,6 +88,8 @@ def _cheapest_splits(d):
             splits = -(-tiles // ct)
             padded = (splits + 7) // 8 * 8 if d["B"] < 8 and splits >= 8 else splits
             wgs = (d["B"] + 7) // 8 * d["D"] * halves * splits if d["B"] >= 8 else (nodes * halves * padded + 7) // 8
+            if s > least and (_max_keys(d) < 512 or nodes >= 256):
+                break  # too few keys, or enough workgroups without a split
             if wgs > slots and not (halves == 1 and s == least):
                 break  # one round of workgroups, or the fewest splits in as many as they take
             c = f(-(-wgs // slots)) * (f(fixed[halves - 1]) + f(tile[halves - 1]) * f(ct))
@@ -147,3 +149,15 @@ def test_noalloc_limit_to_the_byte():
             dims.append(d)
     for d, got in zip(dims, _sizes_of(dims)):
         assert 0 < got <= limit, (d, got)
+
+
+def test_no_split_where_short_rows_would_pay_for_it():
+    """Up to 511 keys a node, or 256 nodes or more: one split, whatever the rest."""
+    dims = [_dims(H, B, D, mk - D - 128 - 3, 399)  # 3 HCA entries
+            for H in (8, 64) for B, D in ((1, 1), (4, 8), (30, 8), (255, 1)) for mk in (300, 459, 511)]
+    dims += [_dims(8, B, D, 512, 8192) for B, D in ((16, 16), (32, 8), (64, 4), (128, 2), (64, 8))]
+    for d, got in zip(dims, _sizes_of(dims)):
+        assert got == _total(d, 1), d
+    more = [_dims(8, 4, 8, 512 - 139, 399), _dims(8, 255, 1, 512, 8192), _dims(64, 4, 4, 512, 8192)]
+    for d, got in zip(more, _sizes_of(more)):
+        assert got > _total(d, 1), d
