@@ -47,17 +47,40 @@ def test_topk_edges(kind, topk):
     assert np.mean(sel != s2) < 0.01  # its own scratch: near ties only
 
 
+SEG = 512 * 33
+
+
+def _committed_scores(w, b, i):
+    """Node i's scores of the committed entries of row b, in float64."""
+    n = w.lens[b] // w.dims["ratio_csa"]
+    k = O.bf16_to_f64(w.c4_idx[w.c4_base[b]:w.c4_base[b] + n])
+    q, wgt = O.bf16_to_f64(w.q_idx[b, i]), O.bf16_to_f64(w.w_idx[b, i])
+    return (wgt[:, None] * np.maximum(q @ k.T, 0)).sum(0)
+
+
+def _span_bits(scores, topk):
+    """At least this many bits has the merge's largest distance: from the best
+    key to the topk-th of the full segment that ends best."""
+    u = (scores.astype(np.float32) + np.float32(0)).view(np.uint32).astype(np.int64)
+    keys = np.where(u >> 31, u, u ^ 0x7FFFFFFF)
+    ends = [np.partition(keys[s:s + SEG], topk - 1)[topk - 1] for s in range(0, len(keys), SEG)
+            if len(keys[s:s + SEG]) > topk]
+    return int(min(ends) - keys.min() + 1).bit_length()
+
+
 @pytest.mark.parametrize("topk", [33, 2047])
 def test_merge_across_zero(topk):
-    """Segmented nodes whose scores straddle zero, many of them exactly zero:
-    the survivors' distances span most of the 32 bits (the merge's wide first
-    digit) and the threshold is a tie."""
+    """Segmented nodes whose scores straddle zero: with a topk past the positive
+    ones the survivors' distances span more than 26 bits (the merge's wide first
+    digit), with a small one those of some nodes do."""
     from paper_2609_24698_amd import DeviceRound
 
     w = synth.make_workload("C0", seed=340 + topk, B=2, D=3, lens=[4 * 33800 + 1, 4 * 17000], tree="random", topk=topk)
     w.w_idx[:, :, 1:] |= 0x8000  # head 0 alone can raise a score
     w.w_idx[:, :, 0] &= 0x7FFF
     nodes = [(b, i) for b in range(w.B) for i in range(w.D)]
+    wide = [_span_bits(_committed_scores(w, b, i), topk) > 26 for b, i in nodes]
+    assert all(wide) if topk == 2047 else any(wide) and not all(wide)
     ref = O.run_round(w, nodes)
 
     def rerun(b, i, chosen):
@@ -65,3 +88,23 @@ def test_merge_across_zero(topk):
 
     print("topk", topk, flush=True)
     _check_stages(w, ref, DeviceRound(w, "cuda:0"), nodes, rerun=rerun)
+
+
+@pytest.mark.parametrize("topk", [33, 2047])
+def test_merge_of_equal_keys(topk):
+    """Half of the scores are zero and none is above: every survivor has the same
+    key, and the node keeps the first topk of them."""
+    from paper_2609_24698_amd import DeviceRound
+
+    w = synth.make_workload("C0", seed=360 + topk, B=2, D=3, lens=[4 * 33800, 4 * 17000], tree="random", topk=topk)
+    w.w_idx[:, :, 1:] = 0
+    w.w_idx[:, :, 0] |= 0x8000
+    print("topk", topk, flush=True)
+    r = DeviceRound(w, "cuda:0")
+    r.mask(), r.compress(), r.verify()
+    torch.cuda.synchronize()
+    sel = r.host("sel")
+    for b in range(w.B):
+        for i in range(w.D):
+            zeros = np.nonzero(_committed_scores(w, b, i) == 0)[0]
+            assert len(zeros) > SEG // 3 and np.array_equal(sel[b, i], zeros[:topk]), (b, i)

@@ -6,8 +6,9 @@ the smallest keys, padding is all ones.  Up to three digits are counted (11,
 the digits found so far, until the bin of the k-th key holds exactly the keys
 still needed; padding is counted like any key.  The merge of a segmented node
 first bounds the keys (no segment's k best exceed its own threshold bin) and
-takes the digits of the distance to the best key.  Both must give exactly the
-k smallest keys, ties to the lower index.
+takes the digits of the distance to the best key, the wide first digit where
+the distances have more than 26 bits.  Both must give exactly the k smallest
+keys, ties to the lower index.
 """
 import numpy as np
 import pytest
@@ -76,14 +77,27 @@ def test_threshold_equals_sort(kind, widths):
         assert np.array_equal(_taken(keys, _threshold(keys, k, widths)), _by_sort(keys, k))
 
 
-@pytest.mark.parametrize("kind", KINDS)
+def _merge_draw(kind, n, rng):
+    if kind.startswith("span"):  # distances of a given number of bits, the best key anywhere
+        bits = int(kind[4:])
+        lo = int(rng.integers(0, PAD - (1 << bits) + 1))
+        return lo + rng.integers(0, (1 << bits) - 1, size=n)
+    return _draw(kind, n, rng)
+
+
+MERGE_KINDS = KINDS + ["span26", "span27", "span30", "span31"]
+
+
+@pytest.mark.parametrize("kind", MERGE_KINDS)
 def test_merge_equals_sort(kind):
-    rng = np.random.default_rng(KINDS.index(kind) + 23)
+    rng = np.random.default_rng(MERGE_KINDS.index(kind) + 23)
+    seen = set()
     for _ in range(60):
         seg, nseg, k = int(rng.integers(40, 400)), int(rng.integers(2, 9)), int(rng.integers(1, 300))
         n = seg * (nseg - 1) + int(rng.integers(1, seg + 1))
-        keys = _draw(kind, n, rng)
-        slots, index, bound, total = [], [], PAD - 1, 0
+        k = min(k, seg - 1)  # a full segment has more candidates than a node keeps
+        keys = _merge_draw(kind, n, rng)
+        slots, index, bound = [], [], PAD - 1
         for s in range(nseg):
             part = keys[s * seg:(s + 1) * seg]
             if len(part) <= k:
@@ -97,7 +111,6 @@ def test_merge_equals_sort(kind):
             row[:len(got)] = part[got]
             slots.append(row)
             index.append(np.concatenate([got + s * seg, np.full(k - len(got), -1)]))
-            total += len(got)
         slots, index = np.concatenate(slots), np.concatenate(index)
         best = int(slots.min())
         worst = max(min(bound, PAD - 1), best)
@@ -105,5 +118,9 @@ def test_merge_equals_sort(kind):
         pad = (1 << bits) - 1
         dist = np.where(slots <= worst, slots - best, pad)
         assert dist[slots <= worst].max() < pad
-        t = (pad - 1, PAD, 0, True) if total <= k else _threshold(dist, k, (11, 11, 10), bits)
-        assert np.array_equal(index[_taken(dist, t, pad)], _by_sort(keys, min(k, n)))
+        seen.add(bits)
+        t = _threshold(dist, k, (13, 11, 8) if bits > 26 else (11, 11, 10), bits)
+        assert np.array_equal(index[_taken(dist, t, pad)], _by_sort(keys, k))
+    wide = {"uniform": True, "scores": True, "last_bin": False, "ties": False, "all_equal": False, "span26": False,
+            "span27": True, "span30": True, "span31": True}[kind]
+    assert any(b > 26 for b in seen) if wide else all(b <= 26 for b in seen), seen
