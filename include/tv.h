@@ -337,12 +337,13 @@ typedef struct {
  * that order on `stream` with the same arguments.  The indexer scoring reads
  * only committed CSA keys and the indexer queries, neither the masks nor the
  * compression's output, so where its fast path applies (H_idx = 8, D <= 8)
- * it runs in the same kernel launch as the mask.  With a flat pool and CSA
- * blocks of at most 4 tokens, the compression needs no launch of its own
- * either: each CSA entry is pooled by one wavefront in the mask's launch
- * (from the parent array, not the masks being written), and each HCA entry,
- * which the top-k does not read, by a workgroup in the top-k's launch
- * (overlap of independent device work, Sec. 4.3).  Everything runs on `stream`, in order
+ * it runs in the same kernel launch as the mask.  There, with CSA blocks of at
+ * most 4 tokens, the compression needs no launch of its own either: each CSA
+ * entry is pooled by one wavefront in the mask's launch (from the parent array,
+ * not the masks being written), and each HCA entry, which the top-k does not
+ * read, by a workgroup in the top-k's launch (overlap of independent device
+ * work, Sec. 4.3); rows of a paged pool that lack a page of an open block are
+ * failed in the mask's launch.  Everything runs on `stream`, in order
  * with earlier and later work on it.  The selection inputs of `round`
  * (draft_tokens, target_logits, ...) and accepted_last, accept_nodes,
  * accept_len are not used.  With round->parents NULL the mask is not built:

@@ -406,15 +406,15 @@ static tv_status verify_impl(const tv_dims *dims, const tv_cache *cache, const u
 
 // One layer's verify preprocess (with_mask), compression and verification.
 // With the scoring's fast path and the split compression, no kernel of its own
-// is left for the compression (a paged step of 12 rows spent 7.7 us in it): the first launch runs the
-// mask (with_mask), the CSA entries (a wavefront per node; beside the mask
-// from the parent array) and the indexer scoring (it reads neither the masks
-// nor the scratch), and the top-k's launch also runs the HCA entries (the
-// top-k only lists their addresses).  With the mask and the scoring's fast
-// path otherwise, the mask and the scoring share a launch before the
-// compression.  Otherwise the calls' kernels in the calls' order.  Every part computes what it computes
-// in the separate calls, so the results are the same bits.  Arguments already
-// checked.
+// is left for the compression (a paged step of 12 rows spent 7.7 us in it): the
+// first launch runs the mask (with_mask), the CSA entries (a wavefront per
+// node; beside the mask from the parent array) and the indexer scoring (it
+// reads neither the masks nor the scratch), and the top-k's launch also runs
+// the HCA entries (the top-k only lists their addresses).  With the mask and
+// the scoring's fast path otherwise, the mask and the scoring share a launch
+// before the compression.  Otherwise the calls' kernels in the calls' order.
+// Every part computes what it computes in the separate calls, so the results
+// are the same bits.  Arguments already checked.
 static tv_status layer_step(const tv_dims *d, const tv_round &r, const tv_layer &L, const WsLayout &w, bool with_mask,
                             hipStream_t stream) {
   const bool split = score_fast_path(*d) && compress_split(*d);
@@ -607,7 +607,7 @@ static tv_status record_round(const tv_dims *d, const tv_round &r, const tv_laye
     st = tv_select_accepted_path(d, r.parents, r.anc, r.depth, r.draft_tokens, r.target_logits, r.vocab,
                                  r.target_tokens, r.accepted_last, r.next_token, r.row_status, r.select_workspace,
                                  r.select_workspace_bytes, s);
-  // the commits: one launch per group of up to kCommitMaxLayers layers, each row walking its layers in order
+  // the commits: one launch per group of up to kCommitMaxLayers layers; of a row, those before the first that fails it
   for (int l0 = 0; l0 < n && st == TV_OK; l0 += kCommitMaxLayers) {
     CommitLayers ls{};
     ls.n = std::min(n - l0, kCommitMaxLayers);

@@ -113,11 +113,11 @@ __global__ void __launch_bounds__(256) mask_score_kernel(tv_dims d, const int32_
       if (parents)  // beside the mask: ancestors from the parent array
         csa_wave_node<true>(d, c, parents, nullptr, nullptr, csa.tree_u, csa.gate_w, csa.scr_c4, row_status,
                             csa.primary_last, csa.pool_c4, csa.pool_c4_idx, n, sm.paths[wv]);
-      else  // the masks and row status are final
+      else  // the masks are final; on a paged pool these wavefronts still fail rows beside each other
         csa_wave_node<false>(d, c, nullptr, anc, depth, csa.tree_u, csa.gate_w, csa.scr_c4, row_status,
                              csa.primary_last, csa.pool_c4, csa.pool_c4_idx, n, sm.paths[wv], true);
     }
-  } else {
+  } else {  // kStatus false: the row status is written in this launch (by the mask, or on a paged pool above)
     const int k = blk - nmask - ncsa, b = k / chunks_per_row;
     score_h8_chunk<FP8, 4, false>(d, c, q_idx, w_idx, nullptr, scores, score_stride, b, k - b * chunks_per_row,
                                   sm.ss);
