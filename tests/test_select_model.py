@@ -1,62 +1,20 @@
-"""A CPU model of the device top-k's radix select, checked against a sort.
+"""The CPU model of the device top-k's threshold search (test_topk_model) on
+keys that float32 scores cannot be made to have.
 
-The top-k and merge kernels select the k largest order-preserving score keys
-with radix passes of 13-bit digits (the last pass the remaining bits), each
-restricted to the keys that share the digits found so far, and stop once the
-threshold bin holds exactly the keys still needed; an ordered compaction then
-takes the keys above the threshold and the lowest-index keys equal to it.
-Padding slots hold key 0 and are not tested key by key: while the resolved
-prefix is 0 they all fall into bin 0, which starts at minus their count.
-
-The GPU parity tests cannot put the threshold inside that bin: only -inf and
-NaN scores have keys below 2**19, and float32 scoring and the float64 oracle
-do not produce them alike.  This model, written from the description above,
-covers it (keys concentrated in bin 0, ties, padding between real keys) and
-must give exactly the k largest keys, ties to the lower index.
+The kernels select the k best keys with digits of 13, 11 and 8 or of 11, 11 and
+10 bits, padding counted like any key (its key is the worst one); an ordered
+compaction then takes the keys better than the threshold and the lowest-index
+keys equal to it.  The GPU parity tests cannot put the threshold among the worst
+keys, beside the padding: only -inf and NaN scores have such keys, and float32
+scoring and the float64 oracle do not produce them alike.  The model covers it
+(keys concentrated in the last bin, ties, padding between real keys) and must
+give exactly the k best keys, ties to the lower index.  Keys here grow with the
+score and 0 is padding; the model takes their complements.
 """
 import numpy as np
 import pytest
 
-BITS = 13
-
-
-def _radix(keys, n, n_real, k, nt):
-    nr = (n + nt - 1) // nt
-    pool = keys[:nr * nt]
-    n_pad = nr * nt - n_real
-    prefix, pmask, rem, shift = 0, 0, k, 32
-    while shift > 0:
-        nb = min(shift, BITS)
-        sft = shift - nb
-        nbins = 1 << nb
-        h = np.zeros(nbins, dtype=np.int64)
-        if prefix == 0:
-            h[0] -= n_pad
-        m = (pool & pmask) == prefix
-        np.add.at(h, ((pool[m] >> sft) & (nbins - 1)).astype(np.int64), 1)
-        assert h.min() >= 0
-        above, found = 0, None
-        for b in range(nbins - 1, -1, -1):
-            if above < rem <= above + h[b]:
-                found = (b, above, int(h[b]))
-                break
-            above += int(h[b])
-        b, above, c = found
-        prefix |= b << sft
-        pmask |= (nbins - 1) << sft
-        rem -= above
-        shift = sft
-        if c == rem:
-            break
-    return prefix, pmask, rem
-
-
-def _compact(keys, n, prefix, pmask, rem):
-    km = keys[:n] & pmask
-    taken = km > prefix
-    equal = np.nonzero((km == prefix) & (keys[:n] != 0))[0][:rem]
-    taken[equal] = True
-    return np.nonzero(taken)[0]
+from .test_topk_model import PAD, _taken, _threshold
 
 
 def _by_sort(keys, n, k):
@@ -64,8 +22,9 @@ def _by_sort(keys, n, k):
     return np.array(sorted(sorted(real, key=lambda e: (-int(keys[e]), e))[:k]))
 
 
+@pytest.mark.parametrize("widths", [(11, 11, 10), (13, 11, 8)], ids=["narrow", "wide"])
 @pytest.mark.parametrize("kind", ["uniform", "bin0", "tiny_ties", "mixed", "all_equal"])
-def test_radix_select_model_equals_sort(kind):
+def test_radix_select_model_equals_sort(kind, widths):
     rng = np.random.default_rng(["uniform", "bin0", "tiny_ties", "mixed", "all_equal"].index(kind) + 11)
     cases = 0
     for trial in range(160):
@@ -75,7 +34,7 @@ def test_radix_select_model_equals_sort(kind):
         n = int(rng.integers(1, nt * kpt + 1))
         if kind == "uniform":
             v = rng.integers(1, 2**32, size=n)
-        elif kind == "bin0":  # every key below 2**19: the threshold lies in bin 0 of the first pass
+        elif kind == "bin0":  # every key below 2**19: the threshold lies in the padding's bin of the first pass
             v = rng.integers(1, 1 << 19, size=n)
         elif kind == "tiny_ties":
             v = rng.integers(1, 40, size=n)
@@ -91,6 +50,6 @@ def test_radix_select_model_equals_sort(kind):
         if n_real <= k:
             continue
         cases += 1
-        prefix, pmask, rem = _radix(keys, n, n_real, k, nt)
-        assert np.array_equal(_compact(keys, n, prefix, pmask, rem), _by_sort(keys, n, k)), (kind, trial)
+        inv = PAD - keys[:-(-n // nt) * nt].astype(np.int64)  # whole slots of nt threads
+        assert np.array_equal(_taken(inv, _threshold(inv, k, widths)), _by_sort(keys, n, k)), (kind, trial)
     assert cases > 50
