@@ -29,7 +29,8 @@
 // instructions a key.  A selection among 2,048 candidates took 12.1 us in its
 // workgroup with two round trips and four barriers a pass, and takes 6.1; among
 // 8,192 (256 workgroups) 15.9 -> 12.0; of a ragged batch of 512 with up to
-// 16,384 21.4 -> 17.0; the merge of 16 x 2,048 survivors 20 -> 14.4.
+// 16,384 21.4 -> 17.0; a merge launch of 16 x 2,048 survivors 21.0 -> 16.9, with
+// distances of more than 26 bits 22.2 -> 22.5.
 //
 // A node with up to kTopkSeg committed entries is selected by one workgroup.
 // A longer node is cut into segments of kTopkSeg entries: each segment's
@@ -685,7 +686,7 @@ __global__ void __launch_bounds__(NT, 1) topk_merge_kernel(tv_dims d, CacheView 
   const int k = d.topk;
   // One round trip for everything whose address is known from (row, node,
   // lane): the row's state, the node's path, and all of the node's survivor
-  // slots and counts (those of segments the row does not have are dropped
+  // slots and bounds (those of segments the row does not have are dropped
   // once its length is known).
   const int32_t status = row_status[b];
   const int32_t L = c.len[b];
@@ -742,7 +743,8 @@ __global__ void __launch_bounds__(NT, 1) topk_merge_kernel(tv_dims d, CacheView 
   Threshold t;
   // Survivors of both signs span most of the 32 bits (few keys lie far from
   // zero): 11 bits of that put thousands on one counter (6,324 of 30,828 on a
-  // 1M-token node, the merge 27 us), so such nodes take the wide first digit.
+  // 1M-token node, the merge 27 us), so such nodes take the wide first digit
+  // (22.5 us).
   if (bits > kMergeWideBits)
     t = radix_threshold<true, KPT>(key, nr, pad, false, k, bits, sh);
   else
